@@ -1,7 +1,8 @@
 // Per-page key metadata: channel-wise min and max of each page's keys (the page landmark
 // that block top-k selection scores, Sec. 3.3 / Appendix C of arXiv 2606.08446).
 //
-// One workgroup per (sequence, logical page) when rebuilding, or per sequence when
+// k_meta_minmax builds large caches of 16-token pages; k_meta_update does the rest:
+// one workgroup per (sequence, logical page) when rebuilding, or per sequence when
 // updating the pages touched by freshly written tokens.  A thread owns one (KV head,
 // 8-channel slice): it streams the slice of every valid token of the page (16 bytes per
 // token, the 16 threads of a head covering one contiguous 256-byte key row), keeps
@@ -64,6 +65,136 @@ __device__ __forceinline__ void slice_minmax(const uint16_t *__restrict__ src, i
     }
     st16(dst, lo);
     st16(dst + kHeadDim, hi);
+}
+
+typedef short s16x2_t __attribute__((ext_vector_type(2)));
+
+// order16 on the two bf16 patterns of a word, and back (the map is an involution).
+__device__ __forceinline__ s16x2_t order16x2(uint32_t word)
+{
+    const s16x2_t s = __builtin_bit_cast(s16x2_t, word);
+    return s ^ ((s >> (short)15) & (short)0x7fff);
+}
+
+__device__ __forceinline__ uint32_t unorder16x2(s16x2_t s)
+{
+    return __builtin_bit_cast(uint32_t, order16x2(__builtin_bit_cast(uint32_t, s)));
+}
+
+constexpr int kMinmaxThreads = 512;
+constexpr int kMinmaxWaves = kMinmaxThreads / 64;
+constexpr int kMinmaxRows = 256;  // landmark rows a workgroup holds in LDS (128 KiB)
+constexpr size_t kMinmaxLds = (size_t)kMinmaxRows * 2 * kHeadDim * sizeof(uint16_t);
+constexpr int64_t kMinmaxBytes = 1ll << 30;  // key bytes from which the burst kernel is used
+
+// Min/max landmarks of 16-token pages in large builds, `chunk` (at most 64) pages of a sequence
+// for up to kMinmaxRows / chunk KV heads per workgroup.  Memory-bound, and bound by its writes
+// more than by its reads: landmark rows (512 B per 4 KiB of keys) trickling out between the key
+// reads cost the reads a third of their rate.  So a workgroup keeps its rows in LDS and
+// writes them in one burst of non-temporal stores, as large a burst as LDS takes; with one
+// workgroup per CU the workgroups start together and stay in step well enough that bursts
+// meet bursts.  2.8 GB of keys, 350 MB of landmarks: 632 us with a store after each page,
+// 604 / 589 / 565 with bursts of 32 / 64 / 128 KiB (5.6 TB/s; the larger pages write less:
+// 592 -> 530 us with 32 tokens, but 409 -> 434 where lengths differ 30-fold, and nothing from
+// 64 tokens on, so they stay with k_meta_update).
+//
+// A wave takes whole (page, head) blocks: a load instruction reads four consecutive key rows
+// (1 KiB), four of them a block, and the next block is in flight while one is folded.  Lane
+// (r, c) folds channels 8c .. 8c+7 of the rows r mod 4 on packed 16-bit integers; two lane
+// exchanges join the four row classes.  Rows past the length repeat the last valid one.
+__global__ __launch_bounds__(kMinmaxThreads) void k_meta_minmax(
+    const uint16_t *__restrict__ k_cache, const int32_t *__restrict__ block_table,
+    const int32_t *__restrict__ seq_lens, uint16_t *__restrict__ meta, int num_kv_heads,
+    int max_pages, int64_t num_phys, int chunk)
+{
+    constexpr int PS = 16;  // a page is one batch of four loads
+    extern __shared__ u32x4_t s_out[];  // [chunk][heads][32]
+    const int b = blockIdx.y;
+    const int h0 = blockIdx.z * (kMinmaxRows / chunk);
+    const int nh = min(kMinmaxRows / chunk, num_kv_heads - h0);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int r = lane >> 4;
+    const int c = lane & 15;
+    const int32_t *bt = block_table + (int64_t)b * max_pages;
+    const int p0 = blockIdx.x * chunk;
+    // lane i: physical page of page p0 + i, or -1 (absent); requested beside the length
+    int e = bt[p0 + lane < max_pages ? p0 + lane : max_pages - 1];
+    e = e >= 0 && e < num_phys ? e : -1;
+    const int L = clamp_len(seq_lens[b], PS, max_pages);
+    const int n = (L + PS - 1) / PS;
+    if (p0 >= n)
+        return;
+    const int items = min(chunk, n - p0) * nh;  // (page, head) blocks, page-major
+    const int steps = (items - wave + kMinmaxWaves - 1) / kMinmaxWaves;
+    auto issue = [&](int s, u32x4_t (&v)[4]) {  // s < steps: the page lies inside the sequence
+        const int it = wave + kMinmaxWaves * s;
+        const int pg = it / nh;
+        const int h = h0 + it - pg * nh;
+        const int ph = __builtin_amdgcn_readlane(e, pg);
+        const int valid = min(PS, L - (p0 + pg) * PS);
+        const uint16_t *src =  // (an absent page reads page 0)
+            k_cache + ((int64_t)(ph < 0 ? 0 : ph) * num_kv_heads + h) * PS * kHeadDim + 8 * c;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = 4 * j + r;
+            v[j] = ld16_nt(src + (row < valid ? row : valid - 1) * kHeadDim);
+        }
+    };
+    auto fold = [&](int s, const u32x4_t (&v)[4]) {
+        s16x2_t mn[4], mx[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            mn[w] = mx[w] = order16x2(v[0][w]);
+#pragma unroll
+        for (int j = 1; j < 4; ++j)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const s16x2_t x = order16x2(v[j][w]);
+                mn[w] = __builtin_elementwise_min(mn[w], x);
+                mx[w] = __builtin_elementwise_max(mx[w], x);
+            }
+        u32x4_t out;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+#pragma unroll
+            for (int x = 16; x < 64; x <<= 1) {
+                const int lo = __shfl_xor(__builtin_bit_cast(int, mn[w]), x, 64);
+                const int hi = __shfl_xor(__builtin_bit_cast(int, mx[w]), x, 64);
+                mn[w] = __builtin_elementwise_min(mn[w], __builtin_bit_cast(s16x2_t, lo));
+                mx[w] = __builtin_elementwise_max(mx[w], __builtin_bit_cast(s16x2_t, hi));
+            }
+            out[w] = unorder16x2(r & 1 ? mx[w] : mn[w]);
+        }
+        if (lane < 32)  // lanes 0-15 the min row, 16-31 the max row
+            s_out[(wave + kMinmaxWaves * s) * 32 + lane] = out;
+    };
+    u32x4_t nxt[4];
+    if (steps > 0)
+        issue(0, nxt);
+    int s = 0;
+    for (; s + 1 < steps; ++s) {
+        u32x4_t cur[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            cur[j] = nxt[j];
+        issue(s + 1, nxt);
+        fold(s, cur);
+    }
+    if (s < steps)
+        fold(s, nxt);
+    __syncthreads();
+    // the burst: a wave writes two landmark rows (1 KiB) per instruction (every lane takes part
+    // in the exchange of the page's entry, also past the last row)
+    for (int it0 = 2 * wave; it0 < items; it0 += 2 * kMinmaxWaves) {
+        const int it = it0 + (lane >> 5);
+        const int pg = (it < items ? it : items - 1) / nh;
+        const int ph = __shfl(e, pg, 64);
+        if (it < items && ph >= 0)
+            __builtin_nontemporal_store(s_out[it * 32 + (lane & 31)],
+                                        reinterpret_cast<u32x4_t *>(meta) + (lane & 31) +
+                                            ((int64_t)ph * num_kv_heads + h0 + it - pg * nh) * 32);
+    }
 }
 
 // Key sums of one (page, head, 8-channel slice) over `valid` tokens, in token order.
@@ -146,6 +277,23 @@ hipError_t launch_ps(const sparrow_shape_t &s, const void *k_cache, const int32_
                      const int32_t *lens, const int32_t *first_pos, void *meta, hipStream_t st)
 {
     const int rebuild = first_pos == nullptr;
+    const int64_t page_bytes = (int64_t)s.num_kv_heads * PS * kHeadDim * 2;
+    // A large build by bursts.  Below about 1 GiB of keys the shorter chain of the
+    // page-per-workgroup kernel wins: one 4096-token sequence 9.5 us against 10.7, 16
+    // sequences of 4K-24K tokens (0.9 GB) 90.5 us either way.
+    if (PS == 16 && rebuild && s.landmark == SPARROW_LANDMARK_MINMAX &&
+        page_bytes * s.max_pages_per_seq * s.batch >= kMinmaxBytes) {
+        int chunk = kMinmaxRows / (s.num_kv_heads < kMinmaxRows ? s.num_kv_heads : kMinmaxRows);
+        chunk = chunk < 64 ? chunk : 64;  // one lane per page
+        const int heads = kMinmaxRows / chunk;  // per workgroup
+        const dim3 grid((s.max_pages_per_seq + chunk - 1) / chunk, s.batch,
+                        (s.num_kv_heads + heads - 1) / heads);
+        hipLaunchKernelGGL(k_meta_minmax, grid, dim3(kMinmaxThreads), kMinmaxLds, st,
+                           static_cast<const uint16_t *>(k_cache), bt, lens,
+                           static_cast<uint16_t *>(meta), s.num_kv_heads, s.max_pages_per_seq,
+                           s.num_phys_pages, chunk);
+        return hipGetLastError();
+    }
     const dim3 grid = rebuild ? dim3(s.max_pages_per_seq, s.batch) : dim3(s.batch);
     if (s.landmark == SPARROW_LANDMARK_MEAN)
         hipLaunchKernelGGL((k_meta_update<PS, true>), grid, dim3(kMetaThreads), 0, st,
