@@ -279,15 +279,22 @@ int sparrow_decode_step(const sparrow_shape_t *shape, const void *q, const void 
     const hipStream_t st = static_cast<hipStream_t>(stream);
     float *scores = static_cast<float *>(workspace);
     void *attn_ws = static_cast<char *>(workspace) + round256(score_topk_workspace(*shape));
-    hipError_t e = launch_page_score(*shape, q, meta, block_table, seq_lens, sched, k_max, scores,
-                                     app, st);
-    if (e != hipSuccess)
-        return SPARROW_EHIP;
-    if (attention_unit_path(*shape, k_max))
+    hipError_t e;
+    if (attention_unit_path(*shape, k_max)) {
+        if (score_select_path(*shape))
+            return status_of(launch_decode_unit(*shape, q, k_cache, v_cache, meta, block_table,
+                                                seq_lens, sched, k_max, out_k, out_idx, scale,
+                                                out, out_dtype, app, st));
+        e = launch_page_score(*shape, q, meta, block_table, seq_lens, sched, k_max, scores, app,
+                              st);
+        if (e != hipSuccess)
+            return SPARROW_EHIP;
         return status_of(launch_select_attention(*shape, q, k_cache, v_cache, block_table,
                                                  seq_lens, sched, k_max, scores, out_k, out_idx,
                                                  scale, out, out_dtype, st));
-    e = launch_topk(*shape, seq_lens, sched, k_max, scores, out_k, out_idx, st);
+    }
+    e = launch_score_topk(*shape, q, meta, block_table, seq_lens, sched, k_max, out_k, out_idx,
+                          scores, app, st);
     if (e != hipSuccess)
         return SPARROW_EHIP;
     return status_of(launch_attention(*shape, plan_attention(*shape), q, k_cache, v_cache,

@@ -31,6 +31,7 @@
 #include <atomic>
 
 #include "common.h"
+#include "score_unit.h"
 #include "topk.h"
 #include "wave.h"
 
@@ -777,6 +778,83 @@ __global__ __launch_bounds__(kUnitThreads) void k_select_attn_unit(AttnArgs a, S
                 [&](int p) { return s_sel[p < kUnitMaxList ? p : kUnitMaxList - 1]; });
 }
 
+// The whole decode step of one unit in one workgroup: the append, the scores (UnitScorer, kept
+// as keys in LDS), the budget, the top-k and the attention.  Every part is the one that the
+// separate kernels run, so the results equal theirs bit for bit.  The attention reads the
+// appended rows from the cache: this workgroup wrote them (the unit's own rows), before the
+// barriers of the selection.  A chain of latencies at this size; against the scoring kernel
+// followed by k_select_attn_unit it saves a launch and the scores' round trip (us per step,
+// 1024-token budget: 8 units x 64 pages 17.5 -> 15.0, 8 x 256 22.1 -> 19.8, 128 x 256 31.3 ->
+// 27.2, 128 x 1024 39.6 -> 37.9, 256 x 1024 55.0 -> 48.3, 128 x 2048 50.5 -> 52.9: the line
+// between the two is score_select_path's).
+template <bool kAppend, bool kMean>
+__global__ __launch_bounds__(kUnitThreads) void k_decode_unit(AttnArgs a, ScoreArgs sa,
+                                                              int32_t *__restrict__ out_k,
+                                                              int32_t *__restrict__ out_idx)
+{
+    // s_o holds the top-k keys first (n <= kUnitBtLds of them), then the waves' o
+    __shared__ float s_o[kUnitWaves * kUnitMaxGroup * kUnitRow];
+    __shared__ float s_m[kUnitWaves * kUnitMaxGroup];
+    __shared__ float s_l[kUnitWaves * kUnitMaxGroup];
+    __shared__ int32_t s_bt[kUnitBtLds];
+    __shared__ int32_t s_sel[kUnitMaxList];
+    __shared__ TopkLds t;
+    static_assert(kUnitWaves * kUnitMaxGroup * kUnitRow >= kUnitBtLds, "the keys fit s_o");
+    const int Hkv = a.num_kv_heads;
+    const int unit = blockIdx.x;
+    const int b = unit / Hkv;
+    const int h = unit - b * Hkv;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int L_raw = a.seq_lens[b];
+
+    UnitScorer<kAppend, kMean, kUnitThreads> s(sa, b, h);
+    u32x4_t nxt[8];
+    uint32_t ab;
+    s.start();
+    bf16x8_t qf[4];
+    load_q(a, b, h, lane & 15, lane >> 4, qf);
+    stage_block_table(a, b, s_bt);
+
+    const int L = clamp_len(L_raw, a.ps, a.max_pages);
+    const int n = (L + a.ps - 1) / a.ps;
+    // (a sequence whose pages may all be kept waits for its budget before it reads landmarks)
+    const bool scored = n > a.k_max;
+    if (scored)
+        s.issue(0, nxt, ab);
+    int last = -1;
+    u32x4_t upd = {0u, 0u, 0u, 0u};
+    if (kAppend && s.append_here(L_raw, n)) {
+        const int64_t phys = s.bt[n - 1];
+        if (phys >= 0 && phys < a.num_phys) {  // else outside the cache: no append
+            upd = append_token<kMean>(sa, b, h, phys, L - 1 - (n - 1) * a.ps, s.li);
+            last = n - 1;
+        }
+    }
+    const int k = budget_pages(L, a.ps, sa.sched, a.k_max);  // <= kUnitMaxList
+    if (h == 0 && tid == 0)
+        out_k[b] = k;
+    if (k >= n) {  // every page kept (k == n; also n == 0): nothing to score
+        if (tid < n)
+            s_sel[tid] = tid;
+    } else {
+        uint32_t *keys = reinterpret_cast<uint32_t *>(s_o);
+        uint32_t kmin = 0xffffffffu, kmax = 0u;
+        if (!scored)
+            s.issue(0, nxt, ab);
+        s.run(nxt, ab, L, n, last, upd, keys, kmin, kmax);
+        block_topk<kUnitThreads>(keys, n, k, kmin, kmax, t,
+                                 [&](uint32_t pos, int i) { s_sel[pos] = i; });
+    }
+    __syncthreads();  // s_sel complete; the keys are dead, s_o is free for the merge
+
+    int32_t *row = out_idx + (int64_t)unit * a.k_max;
+    for (int i = tid; i < a.k_max; i += kUnitThreads)
+        row[i] = i < k ? s_sel[i] : -1;
+    unit_attend(a, b, h, L, k, qf, s_bt, s_o, s_m, s_l,
+                [&](int p) { return s_sel[p < kUnitMaxList ? p : kUnitMaxList - 1]; });
+}
+
 // Merges the partials of a query-head row whose (sequence, KV head) unit spans several waves,
 // and writes zero rows for sequences without pages.  A half-wave (32 lanes, 4 channels per
 // lane) per query-head row, 8 rows per 256-thread workgroup, no LDS.  Segments are taken
@@ -1021,6 +1099,27 @@ hipError_t launch_select_attention(const sparrow_shape_t &s, const void *q, cons
     const int64_t units = (int64_t)s.batch * s.num_kv_heads;
     hipLaunchKernelGGL(k_select_attn_unit, dim3((unsigned)units), dim3(kUnitThreads), 0, stream,
                        a, sel);
+    return hipGetLastError();
+}
+
+hipError_t launch_decode_unit(const sparrow_shape_t &s, const void *q, void *k_cache,
+                              void *v_cache, void *meta, const int32_t *block_table,
+                              const int32_t *seq_lens, const Sched &sched, int32_t k_max,
+                              int32_t *out_k, int32_t *out_idx, float scale, void *out,
+                              int out_dtype, const AppendArgs &app, hipStream_t stream)
+{
+    AttnPlan none{};
+    const AttnArgs a = make_args(s, none, q, k_cache, v_cache, block_table, seq_lens, out_k,
+                                 out_idx, k_max, scale, out, out_dtype, nullptr);
+    const ScoreArgs sa{static_cast<const uint16_t *>(q), static_cast<uint16_t *>(meta),
+                       block_table, seq_lens, sched, app, k_max, s.num_q_heads, s.num_kv_heads,
+                       s.page_size, s.max_pages_per_seq, s.num_phys_pages};
+    const bool mean = s.landmark == SPARROW_LANDMARK_MEAN;
+    auto kernel = app.k_new != nullptr
+                      ? (mean ? k_decode_unit<true, true> : k_decode_unit<true, false>)
+                      : (mean ? k_decode_unit<false, true> : k_decode_unit<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(s.batch * s.num_kv_heads)), dim3(kUnitThreads), 0,
+                       stream, a, sa, out_k, out_idx);
     return hipGetLastError();
 }
 

@@ -178,6 +178,8 @@ struct AppendArgs {
     void *v_cache;
 };
 
+// Whether scoring and selection run in one workgroup per (sequence, KV head) unit.
+bool score_select_path(const sparrow_shape_t &s);
 size_t score_topk_workspace(const sparrow_shape_t &s);
 // Scores of every page into `scores` [batch][num_kv_heads][max_pages] (with the append when
 // app.k_new != nullptr); sequences whose budget keeps every page are skipped.
@@ -235,5 +237,12 @@ hipError_t launch_select_attention(const sparrow_shape_t &s, const void *q, cons
                                    const int32_t *seq_lens, const Sched &sched, int32_t k_max,
                                    const float *scores, int32_t *out_k, int32_t *out_idx,
                                    float scale, void *out, int out_dtype, hipStream_t stream);
+
+// The whole step of such a problem in one launch (append, scores, selection, attention).
+hipError_t launch_decode_unit(const sparrow_shape_t &s, const void *q, void *k_cache,
+                              void *v_cache, void *meta, const int32_t *block_table,
+                              const int32_t *seq_lens, const Sched &sched, int32_t k_max,
+                              int32_t *out_k, int32_t *out_idx, float scale, void *out,
+                              int out_dtype, const AppendArgs &app, hipStream_t stream);
 
 }  // namespace sparrow

@@ -11,6 +11,9 @@
 // written as fp32 to the workspace; sequences whose budget covers every page are skipped.
 // A page whose block-table entry lies outside the cache is absent: score 0, nothing read.
 //
+// Most problems run k_score_select instead: one workgroup scores a whole unit (score_unit.h)
+// into LDS and selects from there.  The split pair below serves few units with long rows.
+//
 // k_topk: one workgroup per (sequence, KV head) - 512 threads, or 256 from 1024 units on -
 // selects the k largest scores with ties to the lower page index.  Scores become
 // order-preserving uint32 keys in LDS; a radix select over 8-bit digits (from the highest
@@ -19,7 +22,10 @@
 // count == T) then places every kept page at its rank in ascending page order.  That
 // select-and-rank core is block_topk (topk.h), shared with the attention kernel that selects
 // and attends in one workgroup for small problems.
+#include <type_traits>
+
 #include "common.h"
+#include "score_unit.h"
 #include "topk.h"
 #include "wave.h"
 
@@ -34,65 +40,12 @@ constexpr int kScoreSmallGrid = 256;  // below this many 32-page workgroups: 8-p
 constexpr int kScoreBatch = 8;   // pages per load batch of a wave
 constexpr int kScoreHeads = 8;   // KV heads per workgroup (at most)
 constexpr int kTopkManyUnits = 1024;  // from this many units on: 256-thread workgroups
+// k_score_select runs 256-thread workgroups from this many units on with at most this many
+// pages (1024 units x 128 pages: 15.0 us against 22.4 with 512 threads, 512 x 512 26.1 against
+// 26.6), else 512-thread ones (1024 x 1170: 114 against 118).
+constexpr int kFusedManyUnits = 512;
+constexpr int kFusedShort = 768;
 constexpr int kTopkBatch = 8;   // score loads in flight per thread
-
-// Sum of 8 per-lane values over the 32 lanes of a half-wave: afterwards lane i holds the
-// total of value (i & 7).  Butterfly: each xor step halves the number of values a lane
-// keeps.  Every value is summed by the same tree of commutative pairwise additions, so
-// identical inputs give identical sums wherever they sit in the batch.
-__device__ __forceinline__ float butterfly8(const float (&v)[8], int li)
-{
-    const bool b0 = li & 1, b1 = li & 2, b2 = li & 4;
-    float v1[4], v2[2];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float keep = b0 ? v[2 * j + 1] : v[2 * j];
-        const float send = b0 ? v[2 * j] : v[2 * j + 1];
-        v1[j] = keep + __shfl_xor(send, 1, 64);
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const float keep = b1 ? v1[2 * j + 1] : v1[2 * j];
-        const float send = b1 ? v1[2 * j] : v1[2 * j + 1];
-        v2[j] = keep + __shfl_xor(send, 2, 64);
-    }
-    const float keep = b2 ? v2[1] : v2[0];
-    const float send = b2 ? v2[0] : v2[1];
-    float r = keep + __shfl_xor(send, 4, 64);
-    r += __shfl_xor(r, 8, 64);
-    r += __shfl_xor(r, 16, 64);
-    return r;
-}
-
-// One lane's share of a page's dot product: its 8 metadata elements against its 8 weights,
-// in a fixed FMA order.
-__device__ __forceinline__ float lane_dot(const float (&w)[8], u32x4_t v)
-{
-    float acc = 0.f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        acc = fmaf(w[2 * t], bf16_lo(v[t]), acc);
-        acc = fmaf(w[2 * t + 1], bf16_hi(v[t]), acc);
-    }
-    return acc;
-}
-
-// Mean landmark: 4 fp32 key sums against the lane's 4 weights, in a fixed FMA order.
-__device__ __forceinline__ float lane_dot4(const float (&w)[8], u32x4_t v)
-{
-    float acc = 0.f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        acc = fmaf(w[t], __uint_as_float(v[t]), acc);
-    return acc;
-}
-
-// Valid tokens of logical page p of a sequence of L tokens.
-__device__ __forceinline__ int page_tokens(int p, int L, int ps)
-{
-    const int left = L - p * ps;
-    return left < ps ? left : ps;
-}
 
 // One workgroup scores kPages (32, or 8 for small grids) consecutive logical pages of one
 // sequence for up to kScoreHeads KV heads.  A wave owns a pair of KV heads: each load instruction reads the
@@ -244,45 +197,11 @@ __global__ __launch_bounds__(kScoreThreads) void k_page_score(
         w[j] = 0.f;
     const uint16_t *qh = q + ((int64_t)b * num_q_heads + (int64_t)(h0 + head) * G) * kHeadDim +
                          (kMean ? 4 * li : i0);
-    auto add_rows = [&](int g0) {
-        u32x4_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            v[u] = (u32x4_t){0u, 0u, 0u, 0u};
-            if (lane_on && g0 + u < G) {
-                if (kMean) {
-                    const u32x2_t x =
-                        *reinterpret_cast<const u32x2_t *>(qh + (g0 + u) * kHeadDim);
-                    v[u][0] = x[0];
-                    v[u][1] = x[1];
-                } else {
-                    v[u] = ld16(qh + (g0 + u) * kHeadDim);
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (!(lane_on && g0 + u < G))
-                continue;
-            if (kMean) {
-                w[0] += bf16_lo(v[u][0]);
-                w[1] += bf16_hi(v[u][0]);
-                w[2] += bf16_lo(v[u][1]);
-                w[3] += bf16_hi(v[u][1]);
-            } else {
-                const bool neg = e0 < kHeadDim;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float x0 = bf16_lo(v[u][j]), x1 = bf16_hi(v[u][j]);
-                    w[2 * j] += neg ? fminf(x0, 0.f) : fmaxf(x0, 0.f);
-                    w[2 * j + 1] += neg ? fminf(x1, 0.f) : fmaxf(x1, 0.f);
-                }
-            }
-        }
-    };
-    add_rows(0);  // straight-line code: these loads go right behind the batch
+    // straight-line code: these loads go right behind the batch
+    const int rows = lane_on ? G : 0;
+    add_query_rows<kMean>(w, qh, 0, rows, e0 < kHeadDim);
     for (int g0 = 8; g0 < G; g0 += 8)
-        add_rows(g0);
+        add_query_rows<kMean>(w, qh, g0, rows, e0 < kHeadDim);
     for (int j0 = 0; j0 < my_pages; j0 += kScoreBatch) {
         u32x4_t cur[kScoreBatch];
 #pragma unroll
@@ -318,6 +237,62 @@ __global__ __launch_bounds__(kScoreThreads) void k_page_score(
             out[last_slot] =
                 kMean ? total / (float)page_tokens(page0 + last_slot, L, ps) : total;
     }
+}
+
+// Scoring, budget and selection of one unit in one workgroup.  HBM-bound on the landmarks; what
+// it saves over the split scoring is the write of the scores (0.8 % of the bytes, but writes
+// into a saturated read stream cost a tenth of its time), the second launch and the top-k's
+// own load of the scores: a unit's keys never leave LDS, and its selection runs while other
+// units' landmarks stream.
+template <bool kAppend, bool kMean, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_score_select(ScoreArgs a,
+                                                           int32_t *__restrict__ out_k,
+                                                           int32_t *__restrict__ out_idx)
+{
+    extern __shared__ uint32_t keys[];  // [max_pages]
+    __shared__ TopkLds t;
+    const int unit = blockIdx.x;
+    const int b = unit / a.num_kv_heads;
+    const int h = unit - b * a.num_kv_heads;
+    const int tid = threadIdx.x;
+    const int L_raw = a.seq_lens[b];
+
+    UnitScorer<kAppend, kMean, kThreads> s(a, b, h);
+    u32x4_t nxt[8];
+    uint32_t ab;
+    s.start();
+
+    const int L = clamp_len(L_raw, a.ps, a.max_pages);
+    const int n = (L + a.ps - 1) / a.ps;
+    // (a sequence whose pages may all be kept waits for its budget before it reads landmarks)
+    const bool scored = n > a.k_max;
+    if (scored)
+        s.issue(0, nxt, ab);
+    int last = -1;
+    u32x4_t upd = {0u, 0u, 0u, 0u};
+    if (kAppend && s.append_here(L_raw, n)) {
+        const int64_t phys = s.bt[n - 1];
+        if (phys >= 0 && phys < a.num_phys) {  // else outside the cache: no append
+            upd = append_token<kMean>(a, b, h, phys, L - 1 - (n - 1) * a.ps, s.li);
+            last = n - 1;
+        }
+    }
+    const int k = budget_pages(L, a.ps, a.sched, a.k_max);
+    if (h == 0 && tid == 0)
+        out_k[b] = k;
+    int32_t *row = out_idx + (int64_t)unit * a.k_max;
+    if (k >= n) {  // every page kept (also n == 0): nothing to score
+        for (int i = tid; i < a.k_max; i += kThreads)
+            row[i] = i < n ? i : -1;
+        return;
+    }
+    if (!scored)
+        s.issue(0, nxt, ab);
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    s.run(nxt, ab, L, n, last, upd, keys, kmin, kmax);
+    block_topk<kThreads>(keys, n, k, kmin, kmax, t, [&](uint32_t pos, int i) { row[pos] = i; });
+    for (int i = k + tid; i < a.k_max; i += kThreads)
+        row[i] = -1;
 }
 
 template <int kTopkThreads>
@@ -390,6 +365,23 @@ size_t score_topk_workspace(const sparrow_shape_t &s)
     return (size_t)s.batch * s.num_kv_heads * s.max_pages_per_seq * sizeof(float);
 }
 
+// One workgroup per unit (k_score_select) reads the landmarks no faster than the split kernel,
+// but writes and re-reads no scores and is one launch; the split kernel spreads a unit over the
+// chip, which few units with long rows need.  Selection with the append, both ways, us (units x
+// pages, split / fused): 8 x 64 11.5 / 7.5, 8 x 256 11.8 / 8.9, 8 x 1024 11.7 / 16.6; 128 x 256
+// 13.3 / 9.7, 128 x 1024 21.7 / 19.9, 128 x 4096 54 / 63; 256 x 4096 99 / 87; 512 x 1335 (mean
+// of a ragged batch) 74 / 68; 1024 x 1170 128 / 114; 2048 x 905 182 / 169; 4096 x 157 93 / 70.
+// Thousands of units with a handful of pages each are better split (4096 x 13 24 / 31, 16384 x
+// 22 97 / 115, 2048 x 13 equal): their workgroups would be nearly empty.
+bool score_select_path(const sparrow_shape_t &s)
+{
+    const int64_t units = (int64_t)s.batch * s.num_kv_heads;
+    if (units > 2048 && s.max_pages_per_seq < 64)
+        return false;
+    return s.max_pages_per_seq <= 512 || units >= 256 ||
+           (units >= 128 && s.max_pages_per_seq <= 2048);
+}
+
 hipError_t launch_page_score(const sparrow_shape_t &s, const void *q, void *meta,
                              const int32_t *block_table, const int32_t *seq_lens,
                              const Sched &sched, int32_t k_max, float *scores,
@@ -441,6 +433,28 @@ hipError_t launch_score_topk(const sparrow_shape_t &s, const void *q, void *meta
                              int32_t *out_idx, void *workspace, const AppendArgs &app,
                              hipStream_t stream)
 {
+    if (score_select_path(s)) {
+        const ScoreArgs a{static_cast<const uint16_t *>(q), static_cast<uint16_t *>(meta),
+                          block_table, seq_lens, sched, app, k_max, s.num_q_heads,
+                          s.num_kv_heads, s.page_size, s.max_pages_per_seq, s.num_phys_pages};
+        const int units = s.batch * s.num_kv_heads;
+        const bool mean = s.landmark == SPARROW_LANDMARK_MEAN;
+        auto go = [&](auto threads) {
+            constexpr int T = decltype(threads)::value;
+            auto kernel = app.k_new != nullptr
+                              ? (mean ? k_score_select<true, true, T> : k_score_select<true, false, T>)
+                              : (mean ? k_score_select<false, true, T>
+                                      : k_score_select<false, false, T>);
+            hipLaunchKernelGGL(kernel, dim3(units), dim3(T),
+                               (size_t)s.max_pages_per_seq * sizeof(uint32_t), stream, a, out_k,
+                               out_idx);
+        };
+        if (units >= kFusedManyUnits && s.max_pages_per_seq <= kFusedShort)
+            go(std::integral_constant<int, 256>{});
+        else
+            go(std::integral_constant<int, 512>{});
+        return hipGetLastError();
+    }
     float *scores = static_cast<float *>(workspace);
     const hipError_t e = launch_page_score(s, q, meta, block_table, seq_lens, sched, k_max,
                                            scores, app, stream);
