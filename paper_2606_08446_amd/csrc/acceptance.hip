@@ -2,17 +2,26 @@
 // Eq. 1 of arXiv 2606.08446) and its lower-tail statistic per length bin (Sec. 3.1-3.2).
 //
 // k_acceptance: alpha_t = sum_x min(p(x), q(x)) with p, q the softmax of the target and draft
-// logit rows at inverse temperature tau.  One 1024-thread workgroup per token (one per CU)
-// makes two passes over its two rows: an online log-sum-exp of both (plain loads), then
-// sum_x exp(min(tau a_x - P, tau b_x - Q)) - one exp per vocabulary entry, since
-// min(e^u, e^v) = e^min(u, v).  The first vectors of the rows stay on chip between the
-// passes, 128 KiB of them in LDS and 12 (fp32) or 10 (bf16) per thread and row in registers
-// (43 % of an fp32 row pair of Qwen3's vocabulary, three quarters of a bf16 one); the
-// rest is read again, with non-temporal loads and from the end of the rows back, so the
-// part read last in the first pass is read first again while the L2 may still hold it.
-// Rows are read as 16-byte vectors; a row that does not start 16-byte aligned is handled
-// with scalar head and tail elements.  Accumulation is fp32 per thread, tree reductions
-// across the workgroup.
+// logit rows at inverse temperature tau.  Two passes over a token's two rows: the log-sum-exp of
+// both, then sum_x exp(min(tau a_x - P, tau b_x - Q)) - one exp per vocabulary entry, since
+// min(e^u, e^v) = e^min(u, v).  A 512-thread workgroup per CU (8 waves, so a wave has 256
+// registers) takes every gridDim.x-th token and keeps as much of the rows as fits on chip
+// between the passes: 144 KiB in LDS, 21 (fp32) or 19 (bf16) vectors per thread and row in
+// registers - 40 % of an fp32 row pair of Qwen3's vocabulary, three quarters of a bf16 one.
+// The rest is read again, last part first, while the L2 may still hold it; where there is a
+// rest, the kept vectors are read non-temporally to leave the caches to it.
+//
+// What bounds it: fp32 rows their traffic (1.5 times the rows, at 7.5 TB/s), bf16 rows the
+// arithmetic and the turns between the passes.  With one token per workgroup the memory was
+// idle while the second pass computed and the VALU idle while a new token's rows arrived;
+// now the second pass replaces every kept vector by the next token's as soon as it is used,
+// the other vectors roll through three slots per row, and one barrier a token joins the
+// passes.  The running maximum went too (lse_add_fast): 4 instructions per entry and row in
+// the first pass instead of 6.  4096 tokens of 151936 entries: bf16 569 -> 465 us, fp32 1050 ->
+// 1026 us; 2000 tokens of 30011: bf16 94 -> 76 us, fp32 135 -> 113 us.
+// Rows are read as 16-byte vectors; the elements before and after them (a row that does not
+// start 16-byte aligned) are one element per thread at most.  Accumulation is fp32 per thread,
+// tree reductions across the workgroup.
 //
 // k_acceptance_topk: the approximation from the top-K listed tokens' normalised
 // log-probabilities, sum_i min(exp(lp_i), exp(lq_i)); one thread per token.
@@ -21,23 +30,26 @@
 // then the order statistics x_lo and x_lo+1 (lo = floor((N - 1) pct / 100)) by a radix
 // select over order-preserving uint32 keys (8-bit digits), and the percentile x_lo + (h - lo)(x_lo+1 - x_lo) in fp64 with the multiply and
 // the add rounded separately.
+#include <type_traits>
+
 #include "common.h"
 #include "wave.h"
 
 namespace sparrow {
 namespace {
 
-constexpr int kAccThreads = 1024;
+constexpr int kAccThreads = 512;
 constexpr int kAccWaves = kAccThreads / 64;
-constexpr int kAccLdsVecs = 4;  // 16-byte vectors of each row a thread keeps in LDS
+constexpr int kAccLdsVecs = 9;  // 16-byte vectors of each row a thread keeps in LDS
+constexpr int kAccBatch = 3;    // vectors of each row a thread has in flight beside the kept ones
+constexpr int kAccSmallVocab = 64;  // rows shorter than this: one wave per token
 constexpr int kTailThreads = 1024;
 constexpr int kTailWaves = kTailThreads / 64;
 
 template <typename T> struct Logit;
 template <> struct Logit<float> {
     static constexpr int kVec = 4;  // elements per 16-byte vector
-    static constexpr int kKeep = 12;  // vectors of each row a thread keeps in registers
-    static constexpr int kBatch = 1;  // vectors of each row per load batch of either pass
+    static constexpr int kKeep = 21;  // vectors of each row a thread keeps in registers
     __device__ static float at(const float *row, int64_t i) { return row[i]; }
     __device__ static void unpack(u32x4_t v, float (&x)[kVec])
     {
@@ -48,8 +60,7 @@ template <> struct Logit<float> {
 };
 template <> struct Logit<uint16_t> {
     static constexpr int kVec = 8;
-    static constexpr int kKeep = 10;  // (measured: the fastest pairs that compile without
-    static constexpr int kBatch = 2;  // spills)
+    static constexpr int kKeep = 19;
     __device__ static float at(const uint16_t *row, int64_t i)
     {
         return __uint_as_float((uint32_t)row[i] << 16);
@@ -77,12 +88,48 @@ struct Lse {
     float m, s;
 };
 
+// A base-2 log-sum-exp m + log2 s as a rounded value and what the rounding left out.  The value
+// is tens where its exponents' differences matter to 2^-23, so its rounding alone was most of
+// the rate's error (4e-7); s is split into exponent and mantissa because log2 of the whole
+// would round at the same place.
+struct LogSum {
+    float hi, lo;
+};
+
+__device__ __forceinline__ LogSum log_sum(Lse a)
+{
+    const int e = __builtin_amdgcn_frexp_expf(a.s);
+    const float f = log2_hw(__builtin_amdgcn_frexp_mantf(a.s));  // in [-1, 0)
+    // two exact sums (Knuth): m + e, then + f
+    const float x = (float)e;
+    const float s = a.m + x, xs = s - a.m;
+    const float r = (a.m - (s - xs)) + (x - xs);
+    const float t = s + f, ft = t - s;
+    return {t, ((s - (t - ft)) + (f - ft)) + r};
+}
+
+// The factor that makes up for the roundings of both rows' log-sum-exps: exact where the two
+// rows share the rate's mass evenly, as they do near 1, and at most the larger of the two roundings off.
+__device__ __forceinline__ float rounding_factor(LogSum p, LogSum q)
+{
+    return exp2_hw(-0.5f * (p.lo + q.lo));
+}
+
 __device__ __forceinline__ Lse lse_merge(Lse a, Lse b)
 {
     const float m = fmaxf(a.m, b.m);
     if (m == -INFINITY)
         return {m, 0.f};
     return {m, a.s * exp2_hw(a.m - m) + b.s * exp2_hw(b.m - m)};
+}
+
+// Moves the reference up to m (>= a.m).
+__device__ __forceinline__ void lse_raise(Lse &a, float m)
+{
+    if (m > a.m) {
+        a.s = a.m == -INFINITY ? 0.f : a.s * exp2_hw(a.m - m);
+        a.m = m;
+    }
 }
 
 // Adds the unscaled values x (scale ts >= 0) to the running log-sum-exp.
@@ -94,10 +141,7 @@ __device__ __forceinline__ void lse_add(Lse &r, const float (&x)[N], float ts)
     for (int e = 1; e < N; ++e)
         mx = fmaxf(mx, x[e]);
     mx *= ts;
-    if (mx > r.m) {
-        r.s = r.m == -INFINITY ? 0.f : r.s * exp2_hw(r.m - mx);
-        r.m = mx;
-    }
+    lse_raise(r, mx);
     // While every entry seen is -inf (masked vocabulary entries), the chunk adds nothing:
     // 2^(x - 0) = 0 for x = -inf, where x - r.m would be -inf - (-inf) = NaN.
     const float m = r.m == -INFINITY ? 0.f : r.m;
@@ -119,26 +163,12 @@ __device__ __forceinline__ void row_split(const T *row, int V, int &head, int &n
     nvec = (V - head) / W;
 }
 
-// Workgroup-wide reduction of a pair of Lse (target, draft) through LDS.
-__device__ void block_lse2(Lse &a, Lse &b, Lse (*s_red)[2])
+// The wave's log-sum-exp, in every lane.
+__device__ __forceinline__ Lse wave_lse(Lse a)
 {
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-        a = lse_merge(a, {__shfl_xor(a.m, x, 64), __shfl_xor(a.s, x, 64)});
-        b = lse_merge(b, {__shfl_xor(b.m, x, 64), __shfl_xor(b.s, x, 64)});
-    }
-    const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        s_red[wave][0] = a;
-        s_red[wave][1] = b;
-    }
-    __syncthreads();
-    a = s_red[0][0];
-    b = s_red[0][1];
-    for (int w = 1; w < kAccWaves; ++w) {
-        a = lse_merge(a, s_red[w][0]);
-        b = lse_merge(b, s_red[w][1]);
-    }
+    const float m = wave_max_f(a.m);
+    const float s = wave_sum_f(a.m == -INFINITY ? 0.f : a.s * exp2_hw(a.m - m));
+    return {m, s};
 }
 
 // Logit as read, negated when the inverse temperature is negative (so that the scale ts
@@ -147,6 +177,25 @@ template <bool kNeg>
 __device__ __forceinline__ float oriented(float x)
 {
     return kNeg ? -x : x;
+}
+
+// A vector's values (as read, scale ts >= 0) into the running log-sum-exp, without the
+// running maximum: the sum is scale free, so the reference m only has to be near the largest
+// terms (a term 2^u with large u carries u's rounding, so u stays below 8 to keep that under
+// 2^-22).  While the vector's own sum is at most 2^8 its entries cost one FMA, one exp and
+// one add each; a larger sum, an infinite one (nothing seen yet: m = -inf) or a NaN (only
+// masked entries seen) takes lse_add, which moves the reference to the vector's maximum.
+template <int N>
+__device__ __forceinline__ void lse_add_fast(Lse &r, const float (&x)[N], float ts)
+{
+    float s = exp2_hw(fmaf(ts, x[0], -r.m));
+#pragma unroll
+    for (int e = 1; e < N; ++e)
+        s += exp2_hw(fmaf(ts, x[e], -r.m));
+    if (s <= 0x1p8f)
+        r.s += s;
+    else
+        lse_add(r, x, ts);
 }
 
 template <typename T, bool kNeg>
@@ -161,8 +210,8 @@ __device__ __forceinline__ void lse_add_vec(Lse &a, Lse &b, u32x4_t va, u32x4_t 
         xa[e] = oriented<kNeg>(xa[e]);
         xb[e] = oriented<kNeg>(xb[e]);
     }
-    lse_add(a, xa, ts);
-    lse_add(b, xb, ts);
+    lse_add_fast(a, xa, ts);
+    lse_add_fast(b, xb, ts);
 }
 
 // sum over the vector's entries of 2^min(ts a - P, ts b - Q)
@@ -181,149 +230,249 @@ __device__ __forceinline__ float min_sum_vec(u32x4_t va, u32x4_t vb, float ts, f
     return acc;
 }
 
-// The row pair's 16-byte vectors v = tid + j * kAccThreads: j < kAccLdsVecs stay in LDS
-// between the passes (s_keep, the thread's own slots), the next Logit<T>::kKeep in this
-// thread's registers, the rest are read again in the second pass.
+// One token's row pair as a thread sees it: 16-byte vectors v = tid + slot * kAccThreads of both
+// rows, and at most one element of the unaligned head or tail.
 template <typename T, bool kNeg>
+struct RowPair {
+    const u32x4_t *pv, *qv;
+    int nvec;
+    bool odd;      // this thread has an element outside the vectors
+    float oa, ob;  // that element of both rows
+
+    __device__ __forceinline__ void open(const T *target, const T *draft, int64_t t, int V)
+    {
+        const T *pr = target + t * V;
+        const T *qr = draft + t * V;
+        int head;
+        row_split(pr, V, head, nvec);
+        const int tail0 = head + nvec * Logit<T>::kVec;
+        const int tid = threadIdx.x;
+        const int i = tid < head ? tid : tail0 + tid - head;  // (head and tail: under 16 each)
+        odd = i < V && (tid < head || i >= tail0);
+        oa = ob = 0.f;
+        if (odd) {
+            oa = oriented<kNeg>(Logit<T>::at(pr, i));
+            ob = oriented<kNeg>(Logit<T>::at(qr, i));
+        }
+        pv = reinterpret_cast<const u32x4_t *>(pr + head);
+        qv = reinterpret_cast<const u32x4_t *>(qr + head);
+    }
+    __device__ __forceinline__ bool has(int slot) const
+    {
+        return (int)threadIdx.x + slot * kAccThreads < nvec;
+    }
+    // The slot's vectors of both rows.  Every load is unconditional: a thread past the row
+    // repeats its last vector, a slot past it reads slot 0.  (The slot's start is uniform, so
+    // a load needs one 32-bit register of its own for its address.)
+    template <bool kOnce>
+    __device__ __forceinline__ void load(int slot, u32x4_t &a, u32x4_t &b) const
+    {
+        int left = nvec - 1 - slot * kAccThreads;
+        const int64_t start = left < 0 ? 0 : (int64_t)slot * kAccThreads;
+        left = left < 0 ? nvec - 1 : left;
+        const uint32_t off = 16u * (uint32_t)min((int)threadIdx.x, left);
+        const char *pa = reinterpret_cast<const char *>(pv + start);
+        const char *pb = reinterpret_cast<const char *>(qv + start);
+        a = kOnce ? ld16_nt(pa + off) : ld16(pa + off);
+        b = kOnce ? ld16_nt(pb + off) : ld16(pb + off);
+    }
+};
+
+template <typename T, bool kNeg, bool kLong>
 __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict__ target,
-                                                            const T *__restrict__ draft, int V,
-                                                            float ts, float *__restrict__ alpha)
+                                                            const T *__restrict__ draft, int tokens,
+                                                            int V, float ts,
+                                                            float *__restrict__ alpha)
 {
     extern __shared__ u32x4_t s_keep[];  // [2][kAccLdsVecs][kAccThreads]
-    __shared__ Lse s_red[kAccWaves][2];
-    __shared__ float s_sum[kAccWaves];
-    constexpr int R = Logit<T>::kKeep, L = kAccLdsVecs, NB = Logit<T>::kBatch;
-    const int64_t t = blockIdx.x;
-    const T *pr = target + t * V;
-    const T *qr = draft + t * V;
+    __shared__ Lse s_red[2][kAccWaves][2];
+    __shared__ float s_sum[2][kAccWaves];
+    constexpr int R = Logit<T>::kKeep, L = kAccLdsVecs, NB = kAccBatch;
+    static_assert(L % NB == 0, "an LDS group is whole");
     const int tid = threadIdx.x;
-    int head, nvec;
-    row_split(pr, V, head, nvec);
-    const int tail0 = head + nvec * Logit<T>::kVec;
-    const u32x4_t *pv = reinterpret_cast<const u32x4_t *>(pr + head);
-    const u32x4_t *qv = reinterpret_cast<const u32x4_t *>(qr + head);
-    const int onchip = (R + L) * kAccThreads;  // vectors of each row held on chip
+    const int wave = tid >> 6;
+    const int lane = tid & 63;
 
-    // ---- pass 1: log-sum-exp of both rows (plain loads), keeping the first vectors: those
-    // for LDS first (their registers are free again before the kept ones are loaded)
-    Lse a{-INFINITY, 0.f}, b{-INFINITY, 0.f};
-    for (int i = tid; i < head; i += kAccThreads) {
-        const float xa[1] = {oriented<kNeg>(Logit<T>::at(pr, i))};
-        const float xb[1] = {oriented<kNeg>(Logit<T>::at(qr, i))};
-        lse_add(a, xa, ts);
-        lse_add(b, xb, ts);
-    }
-    for (int i = tail0 + tid; i < V; i += kAccThreads) {
-        const float xa[1] = {oriented<kNeg>(Logit<T>::at(pr, i))};
-        const float xb[1] = {oriented<kNeg>(Logit<T>::at(qr, i))};
-        lse_add(a, xa, ts);
-        lse_add(b, xb, ts);
-    }
-    {
-        u32x4_t la[L], lb[L];
-#pragma unroll
-        for (int j = 0; j < L; ++j) {
-            const int v = tid + j * kAccThreads;
-            la[j] = lb[j] = (u32x4_t){0u, 0u, 0u, 0u};
-            if (v < nvec) {
-                la[j] = pv[v];
-                lb[j] = qv[v];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < L; ++j) {
-            if (tid + j * kAccThreads < nvec) {
-                lse_add_vec<T, kNeg>(a, b, la[j], lb[j], ts);
-                s_keep[j * kAccThreads + tid] = la[j];
-                s_keep[(L + j) * kAccThreads + tid] = lb[j];
-            }
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);  // the kept vectors' loads stay behind this point
-    u32x4_t ka[R], kb[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const int v = tid + (L + j) * kAccThreads;
-        ka[j] = kb[j] = (u32x4_t){0u, 0u, 0u, 0u};
-        if (v < nvec) {
-            ka[j] = pv[v];
-            kb[j] = qv[v];
-        }
-    }
+    RowPair<T, kNeg> x;
+    u32x4_t ka[R], kb[R];          // slots L .. L + R - 1 of the current token
+    u32x4_t na[NB], nb[NB];        // a group of the others, in flight
+    // Group g of the slots that are not kept: slots g NB .., with the kept ones skipped.
+    auto slot_of = [&](int g, int u) {
+        const int i = g * NB + u;
+        return i < L ? i : i + R;
+    };
+    auto load_loose = [&](const RowPair<T, kNeg> &r, int g, int u, auto again) {
+        r.template load<decltype(again)::value>(slot_of(g, u), na[u], nb[u]);
+    };
+    auto load_kept = [&](const RowPair<T, kNeg> &r, int j) {
+        r.template load<kLong>(L + j, ka[j], kb[j]);
+    };
+    constexpr std::false_type kFirst{};
+    constexpr std::true_type kAgain{};
+
+    int t = blockIdx.x;
+    x.open(target, draft, t, V);
 #pragma unroll
     for (int j = 0; j < R; ++j)
-        if (tid + (L + j) * kAccThreads < nvec)
-            lse_add_vec<T, kNeg>(a, b, ka[j], kb[j], ts);
-    int v = onchip + tid;
-    for (; v + (NB - 1) * kAccThreads < nvec; v += NB * kAccThreads) {
-        u32x4_t ra[NB], rb[NB];
+        load_kept(x, j);
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            ra[u] = pv[v + u * kAccThreads];
-            rb[u] = qv[v + u * kAccThreads];
-        }
-#pragma unroll
-        for (int u = 0; u < NB; ++u)
-            lse_add_vec<T, kNeg>(a, b, ra[u], rb[u], ts);
-    }
-    for (; v < nvec; v += kAccThreads)
-        lse_add_vec<T, kNeg>(a, b, pv[v], qv[v], ts);
-    block_lse2(a, b, s_red);
-    const float P = a.m + log2_hw(a.s);  // base-2 log-sum-exp of the scaled rows
-    const float Q = b.m + log2_hw(b.s);
+    for (int u = 0; u < NB; ++u)
+        load_loose(x, 0, u, kFirst);
 
-    // ---- pass 2: sum of 2^min(ts a - P, ts b - Q) = exp(min(tau a - lse_a, tau b - lse_b)):
-    // the vectors read again first, from the end of the rows back (non-temporal loads), then
-    // those in LDS and in registers
-    float acc = 0.f;
-    for (int i = tid; i < head; i += kAccThreads)
-        acc += exp2_hw(fminf(fmaf(ts, oriented<kNeg>(Logit<T>::at(pr, i)), -P),
-                             fmaf(ts, oriented<kNeg>(Logit<T>::at(qr, i)), -Q)));
-    for (int i = tail0 + tid; i < V; i += kAccThreads)
-        acc += exp2_hw(fminf(fmaf(ts, oriented<kNeg>(Logit<T>::at(pr, i)), -P),
-                             fmaf(ts, oriented<kNeg>(Logit<T>::at(qr, i)), -Q)));
-    const int nre = nvec - onchip;  // vectors read again (none if <= 0)
-    int w = tid;
-    for (; w + (NB - 1) * kAccThreads < nre; w += NB * kAccThreads) {
-        u32x4_t ra[NB], rb[NB];
+    for (int round = 0;; round ^= 1) {
+        const int nslots = (x.nvec + kAccThreads - 1) / kAccThreads;
+        const int loose = nslots <= L ? nslots : (nslots <= L + R ? L : nslots - R);
+        const int groups = (loose + NB - 1) / NB;
+
+        // ---- pass 1: log-sum-exp of both rows
+        Lse a{-INFINITY, 0.f}, b{-INFINITY, 0.f};
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            ra[u] = ld16_nt(pv + (nvec - 1 - (w + u * kAccThreads)));
-            rb[u] = ld16_nt(qv + (nvec - 1 - (w + u * kAccThreads)));
+        for (int j = 0; j < R; ++j) {
+            if (x.has(L + j))
+                lse_add_vec<T, kNeg>(a, b, ka[j], kb[j], ts);
+            if (j == 0) {  // the reference of the whole wave, so few later vectors exceed it
+                lse_raise(a, wave_max_f(a.m));
+                lse_raise(b, wave_max_f(b.m));
+            }
+        }
+        if (x.odd) {
+            const float xa[1] = {x.oa}, xb[1] = {x.ob};
+            lse_add(a, xa, ts);
+            lse_add(b, xb, ts);
+        }
+        // The other slots roll through na, nb: each is replaced by its successor as soon as it
+        // is used, and the last group stays for the second pass, which goes back to front.
+        auto first_use = [&](int g, int u) {
+            if (x.has(slot_of(g, u)))
+                lse_add_vec<T, kNeg>(a, b, na[u], nb[u], ts);
+            if (g < L / NB) {
+                s_keep[(g * NB + u) * kAccThreads + tid] = na[u];
+                s_keep[(L + g * NB + u) * kAccThreads + tid] = nb[u];
+            }
+        };
+        for (int g = 0; g + 1 < groups; ++g) {
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                first_use(g, u);
+                load_loose(x, g + 1, u, kFirst);
+            }
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u)
-            acc += min_sum_vec<T, kNeg>(ra[u], rb[u], ts, P, Q);
+            first_use(groups - 1, u);
+        a = wave_lse(a);
+        b = wave_lse(b);
+        if (lane == 0) {
+            s_red[round][wave][0] = a;
+            s_red[round][wave][1] = b;
+        }
+        __syncthreads();  // (the rounds alternate buffers: one barrier per token)
+        a = s_red[round][0][0];
+        b = s_red[round][0][1];
+#pragma unroll
+        for (int w = 1; w < kAccWaves; ++w) {
+            a = lse_merge(a, s_red[round][w][0]);
+            b = lse_merge(b, s_red[round][w][1]);
+        }
+        const LogSum lp = log_sum(a), lq = log_sum(b);  // of the scaled rows
+        const float P = lp.hi, Q = lq.hi;
+        if (tid == 0 && t != (int)blockIdx.x) {  // the previous token's waves are all in
+            float total = 0.f;
+            for (int w = 0; w < kAccWaves; ++w)
+                total += s_sum[round ^ 1][w];
+            alpha[t - gridDim.x] = total;
+        }
+
+        // ---- pass 2: sum of 2^min(ts a - P, ts b - Q), the other slots first (the last group
+        // is still here), then LDS, then the kept slots, each replaced by the next token's
+        float acc = 0.f;
+        if (x.odd)
+            acc += exp2_hw(fminf(fmaf(ts, x.oa, -P), fmaf(ts, x.ob, -Q)));
+        auto second_use = [&](int g, int u) {
+            if (x.has(slot_of(g, u)))
+                acc += min_sum_vec<T, kNeg>(na[u], nb[u], ts, P, Q);
+        };
+        if (groups > L / NB) {
+            for (int g = groups - 1; g > L / NB; --g) {
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    second_use(g, u);
+                    load_loose(x, g - 1, u, kAgain);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                second_use(L / NB, u);
+        }
+#pragma unroll
+        for (int u = 0; u < L; ++u)
+            if (x.has(u))
+                acc += min_sum_vec<T, kNeg>(s_keep[u * kAccThreads + tid],
+                                            s_keep[(L + u) * kAccThreads + tid], ts, P, Q);
+        const int64_t tn = (int64_t)t + gridDim.x;
+        const bool more = tn < tokens;
+        RowPair<T, kNeg> y = x;
+        if (more) {
+            y.open(target, draft, tn, V);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (x.has(L + j))
+                    acc += min_sum_vec<T, kNeg>(ka[j], kb[j], ts, P, Q);
+                load_kept(y, j);
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                load_loose(y, 0, u, kFirst);
+        } else {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (x.has(L + j))
+                    acc += min_sum_vec<T, kNeg>(ka[j], kb[j], ts, P, Q);
+        }
+        acc = wave_sum_f(acc) * rounding_factor(lp, lq);
+        if (lane == 0)
+            s_sum[round][wave] = acc;
+        if (!more)
+            break;
+        t = (int)tn;
+        x = y;
     }
-    for (; w < nre; w += kAccThreads)
-        acc += min_sum_vec<T, kNeg>(ld16_nt(pv + (nvec - 1 - w)), ld16_nt(qv + (nvec - 1 - w)),
-                                    ts, P, Q);
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-        // (opaque to the compiler, so that it unpacks the kept vectors again here instead of
-        // holding the first pass's unpacked bf16 elements, twice the registers, until now)
-        if constexpr (sizeof(T) == 2)
-            asm volatile("" : "+v"(ka[j]), "+v"(kb[j]));
-        if (tid + (L + j) * kAccThreads < nvec)
-            acc += min_sum_vec<T, kNeg>(ka[j], kb[j], ts, P, Q);
-    }
-#pragma unroll
-    for (int j = 0; j < L; ++j)
-        if (tid + j * kAccThreads < nvec)
-            acc += min_sum_vec<T, kNeg>(s_keep[j * kAccThreads + tid],
-                                        s_keep[(L + j) * kAccThreads + tid], ts, P, Q);
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1)
-        acc += __shfl_xor(acc, x, 64);
-    if ((tid & 63) == 0)
-        s_sum[tid >> 6] = acc;
     __syncthreads();
     if (tid == 0) {
         float total = 0.f;
-        for (int w2 = 0; w2 < kAccWaves; ++w2)
-            total += s_sum[w2];
+        // (the last round's buffer: rounds alternate from 0)
+        const int last = ((tokens - 1 - (int)blockIdx.x) / (int)gridDim.x) & 1;
+        for (int w = 0; w < kAccWaves; ++w)
+            total += s_sum[last][w];
         alpha[t] = total;
     }
+}
+
+// Rows of fewer than kAccSmallVocab entries: one wave per token, one entry per lane.
+template <typename T, bool kNeg>
+__global__ __launch_bounds__(64) void k_acceptance_small(const T *__restrict__ target,
+                                                         const T *__restrict__ draft, int V,
+                                                         float ts, float *__restrict__ alpha)
+{
+    const int64_t t = blockIdx.x;
+    const int i = threadIdx.x;
+    Lse a{-INFINITY, 0.f}, b{-INFINITY, 0.f};
+    float xa[1] = {0.f}, xb[1] = {0.f};
+    if (i < V) {
+        xa[0] = oriented<kNeg>(Logit<T>::at(target + t * V, i));
+        xb[0] = oriented<kNeg>(Logit<T>::at(draft + t * V, i));
+        lse_add(a, xa, ts);
+        lse_add(b, xb, ts);
+    }
+    a = wave_lse(a);
+    b = wave_lse(b);
+    const LogSum lp = log_sum(a), lq = log_sum(b);
+    const float acc =
+        wave_sum_f(i < V ? exp2_hw(fminf(fmaf(ts, xa[0], -lp.hi), fmaf(ts, xb[0], -lq.hi)))
+                         : 0.f) *
+        rounding_factor(lp, lq);
+    if (i == 0)
+        alpha[t] = acc;
 }
 
 __global__ __launch_bounds__(256) void k_acceptance_topk(const float *__restrict__ lp_target,
@@ -557,24 +706,43 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_stats(
 
 }  // namespace
 
+static int device_cus()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1)
+        cus = 256;
+    return cus;
+}
+
 hipError_t launch_acceptance(int64_t T, int V, int dtype, const void *target, const void *draft,
                              float tau, float *alpha, hipStream_t stream)
 {
-    // The vectors kept in LDS between the passes (128 KiB: one workgroup per CU).
+    // The vectors kept in LDS between the passes (144 KiB: one workgroup per CU).
     constexpr size_t kKeep = 2 * (size_t)kAccLdsVecs * kAccThreads * sizeof(u32x4_t);
     const bool neg = tau < 0.f;
     const float ts = (neg ? -tau : tau) * 1.44269504088896340736f;  // |tau| log2(e)
-    const dim3 grid((unsigned)T), block(kAccThreads);
-    if (dtype == SPARROW_LOGITS_BF16) {
-        auto k = neg ? k_acceptance<uint16_t, true> : k_acceptance<uint16_t, false>;
-        hipLaunchKernelGGL(k, grid, block, kKeep, stream,
-                           static_cast<const uint16_t *>(target),
-                           static_cast<const uint16_t *>(draft), V, ts, alpha);
-    } else {
-        auto k = neg ? k_acceptance<float, true> : k_acceptance<float, false>;
-        hipLaunchKernelGGL(k, grid, block, kKeep, stream, static_cast<const float *>(target),
-                           static_cast<const float *>(draft), V, ts, alpha);
-    }
+    auto go = [&](auto type) {
+        using L = decltype(type);
+        const L *p = static_cast<const L *>(target), *q = static_cast<const L *>(draft);
+        if (V < kAccSmallVocab) {
+            hipLaunchKernelGGL((neg ? k_acceptance_small<L, true> : k_acceptance_small<L, false>),
+                               dim3((unsigned)T), dim3(64), 0, stream, p, q, V, ts, alpha);
+            return;
+        }
+        const bool fits =
+            V / Logit<L>::kVec <= (Logit<L>::kKeep + kAccLdsVecs) * kAccThreads;
+        auto kernel = fits ? (neg ? k_acceptance<L, true, false> : k_acceptance<L, false, false>)
+                           : (neg ? k_acceptance<L, true, true> : k_acceptance<L, false, true>);
+        const int cus = device_cus();
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(T < cus ? T : cus)), dim3(kAccThreads), kKeep,
+                           stream, p, q, (int)T, V, ts, alpha);
+    };
+    if (dtype == SPARROW_LOGITS_BF16)
+        go(uint16_t{});
+    else
+        go(float{});
     return hipGetLastError();
 }
 

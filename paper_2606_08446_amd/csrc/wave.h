@@ -85,6 +85,29 @@ __device__ __forceinline__ float half_wave_reduce(float x, float identity, Op op
     return (threadIdx.x & 32) ? hi : lo;
 }
 
+// Maximum / sum over the wave (every lane gets it).
+template <typename Op>
+__device__ __forceinline__ float wave_reduce_f(float x, float identity, Op op)
+{
+    x = op(x, dpp_move_f<kDppRowShr1, 0xf>(x, identity));
+    x = op(x, dpp_move_f<kDppRowShr2, 0xf>(x, identity));
+    x = op(x, dpp_move_f<kDppRowShr4, 0xf>(x, identity));
+    x = op(x, dpp_move_f<kDppRowShr8, 0xf>(x, identity));
+    x = op(x, dpp_move_f<kDppRowBcast15, 0xa>(x, identity));
+    x = op(x, dpp_move_f<kDppRowBcast31, 0xc>(x, identity));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
+__device__ __forceinline__ float wave_max_f(float x)
+{
+    return wave_reduce_f(x, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
+}
+
+__device__ __forceinline__ float wave_sum_f(float x)
+{
+    return wave_reduce_f(x, 0.f, [](float a, float b) { return a + b; });
+}
+
 __device__ __forceinline__ float half_wave_max(float x)
 {
     return half_wave_reduce(x, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
