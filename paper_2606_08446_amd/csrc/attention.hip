@@ -12,7 +12,8 @@
 // Its online-softmax state is flushed whenever its range leaves a (sequence, KV head):
 // a unit whose pages all fall in one wave is normalised and written to `out` directly;
 // otherwise the wave writes a partial (m, l, o) to segment slot `wave + unit` (unique
-// along the partition) and k_attn_merge combines the partials of that unit.
+// along the partition) and k_attn_merge (few units: k_attn_merge_wide) combines
+// the partials of that unit.
 // Small problems (a few units with short lists) take k_attn_unit instead: one workgroup per
 // unit, its waves' states merged in LDS, one launch.
 //
@@ -42,7 +43,8 @@ constexpr int kAttnThreads = 256;
 constexpr int kAttnWaves = kAttnThreads / 64;
 constexpr int kBatch = 64;        // pages per prefetched page-list batch
 constexpr int kMaxWaves = 4096;   // upper bound of streaming waves (sizes the workspace)
-constexpr int kUnitSegments = 64;  // streaming waves per (sequence, KV head) unit, on average
+constexpr int kUnitSegments = 256;  // streaming waves per (sequence, KV head) unit, on average
+constexpr int kFineSegments = 128;  // and up to which a wave may have a single 16-token chunk
 
 struct AttnArgs {
     const uint16_t *q;
@@ -278,12 +280,19 @@ __global__ __launch_bounds__(kAttnThreads) void k_attn_stream(AttnArgs a)
             a.plan_off[b] = s_off[b];
 
     const int64_t P = (int64_t)s_off[B] * Hkv;
-    // One wave per listed page at most, and at most kUnitSegments waves per unit on average:
-    // a unit split over hundreds of one-page waves leaves the merge a long serial chain of
-    // partials (one 4096-token sequence, dense: 33 -> 21 us per step with the cap).
+    // One wave per listed page at most, and on average at most kUnitSegments waves per unit, or
+    // kFineSegments where a wave would have less than two 16-token chunks: the merge reads
+    // one partial per wave, and its time has to stay small against what more waves save.
+    // Kernel times of a dense call with caps of 64 / 128 / 256 / 512, attention + merge in us:
+    // 8 units x 4096 tokens 9.6+3.9 / 7.3+4.9 / 7.2+6.1 / 7.2+5.5, 8 x 16384 27.2+4.6 /
+    // 17.9+4.4 / 15.8+5.5 / 15.9+5.5, 8 x 65536 (5 heads each) 99+4.6 / 55.9+4.9 / 45.4+6.1 /
+    // 45.4+6.0, 2 x 16384 25.6+4.6 / 16.1+4.7 / 11.1+6.2 / 9.4+9.2.
+    const int64_t units = (int64_t)B * Hkv;
     int64_t W = P < a.total_waves ? P : a.total_waves;
-    if (W > (int64_t)B * Hkv * kUnitSegments)
-        W = (int64_t)B * Hkv * kUnitSegments;
+    const int64_t pairs = P * (a.ps >> 4) / 2;
+    const int64_t fine = units * kFineSegments > pairs ? units * kFineSegments : pairs;
+    W = W < fine ? W : fine;
+    W = W < units * kUnitSegments ? W : units * kUnitSegments;
     const int w = blockIdx.x * kAttnWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w >= W)
         return;
@@ -938,6 +947,108 @@ __global__ __launch_bounds__(kMergeThreads) void k_attn_merge(AttnArgs a)
     store_out4(a.out, a.out_bf16, orow, acc * inv);
 }
 
+// The same merge for few units, whose lists are spread over many waves (up to kUnitSegments and
+// one more, or two, each): one workgroup per query-head row.  k_attn_merge is a chain there, one
+// round trip to memory per 16 partials of a row, with two workgroups on the whole chip; here
+// every half-wave takes kWideChunk partials at a time, so 16 half-waves have 128 of them in
+// flight, and the half-waves' (m, l, o) states meet in LDS.  It is bound by the latency of its
+// launch and two dependent round trips.
+constexpr int kWideThreads = 512;
+constexpr int kWideParts = kWideThreads / 32;
+constexpr int kWideChunk = 8;
+// Up to 128 units and 512 rows (two workgroups per CU).  Kernel times, half-wave merge -> this
+// one in us, units x query heads of each: 32 x 4 8.8 -> 4.4, 32 x 16 9.0 -> 6.1, 64 x 2 6.4 ->
+// 4.0, 64 x 8 6.4 -> 5.1, 96 x 2 5.0 -> 4.0, 128 x 4 5.4 -> 4.7, but 64 x 16 7.0 -> 8.4 and
+// 96 x 8 5.3 -> 7.2; a dense call of 192 units x 2 68.0 -> 68.3.
+constexpr int kWideMaxUnits = 128;
+constexpr int kWideMaxRows = 512;
+
+__global__ __launch_bounds__(kWideThreads) void k_attn_merge_wide(AttnArgs a)
+{
+    __shared__ __align__(16) float s_o[kWideParts][kHeadDim];
+    __shared__ float s_m[kWideParts], s_l[kWideParts];
+    const int Hq = a.num_q_heads;
+    const int Hkv = a.num_kv_heads;
+    const int G = Hq / Hkv;
+    const int row = blockIdx.x;  // grid = batch * num_q_heads
+    const int tid = threadIdx.x;
+    const int part = tid >> 5;
+    const int t = tid & 31;
+    const int b = row / Hq;
+    const int j = row - b * Hq;
+    const int h = j / G;
+    const int g = j - h * G;
+    const int unit = b * Hkv + h;
+    const int32_t o0 = a.plan_off[b], o1 = a.plan_off[b + 1];
+    const int wf = a.unit_waves[2 * unit];
+    const int wl = a.unit_waves[2 * unit + 1];
+    if (o1 == o0) {
+        if (part == 0)
+            store_out4(a.out, a.out_bf16, (int64_t)row * kHeadDim + 4 * t,
+                       (f32x4_t){0.f, 0.f, 0.f, 0.f});
+        return;
+    }
+    if (wf == wl)
+        return;  // one wave held the whole unit and wrote its output
+    const int nseg = wl - wf + 1;
+    const int64_t seg0 = (int64_t)wf + unit;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    float M = -INFINITY, lsum = 0.f;
+    for (int c0 = part * kWideChunk; c0 < nseg; c0 += kWideParts * kWideChunk) {
+        const int n = nseg - c0 < kWideChunk ? nseg - c0 : kWideChunk;
+        f32x4_t o[kWideChunk];
+        float m[kWideChunk], l[kWideChunk];
+#pragma unroll
+        for (int i = 0; i < kWideChunk; ++i) {
+            o[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+            m[i] = -INFINITY;
+            l[i] = 0.f;
+            if (i < n) {
+                const int64_t sg = (seg0 + c0 + i) * G + g;
+                o[i] = __builtin_bit_cast(f32x4_t, ld16(a.o_part + sg * kHeadDim + 4 * t));
+                const u32x2_t ml = *reinterpret_cast<const u32x2_t *>(a.ml_part + sg * 2);
+                m[i] = __uint_as_float(ml[0]);
+                l[i] = __uint_as_float(ml[1]);
+            }
+        }
+        float Mn = M;
+#pragma unroll
+        for (int i = 0; i < kWideChunk; ++i)
+            Mn = fmaxf(Mn, m[i]);
+        const float r = M == -INFINITY ? 0.f : exp2f(M - Mn);
+        lsum *= r;
+        acc *= r;
+        M = Mn;
+#pragma unroll
+        for (int i = 0; i < kWideChunk; ++i) {
+            const float f = m[i] == -INFINITY ? 0.f : exp2f(m[i] - Mn);  // no valid pages: 0
+            lsum += f * l[i];
+            acc += f * o[i];
+        }
+    }
+    st16(&s_o[part][4 * t], __builtin_bit_cast(u32x4_t, acc));
+    if (t == 0) {
+        s_m[part] = M;
+        s_l[part] = lsum;
+    }
+    __syncthreads();
+    if (tid >= kHeadDim)
+        return;
+    float top = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < kWideParts; ++p)
+        top = fmaxf(top, s_m[p]);
+    float sum = 0.f, v = 0.f;
+#pragma unroll
+    for (int p = 0; p < kWideParts; ++p) {
+        const float f = s_m[p] == -INFINITY ? 0.f : exp2f(s_m[p] - top);
+        sum += f * s_l[p];
+        v += f * s_o[p][tid];
+    }
+    const float inv = sum > 0.f ? 1.f / sum : 0.f;
+    store_out(a.out, a.out_bf16, (int64_t)row * kHeadDim + tid, v * inv);
+}
+
 // Streaming waves on the current device: compute units x resident workgroups x 4, capped.
 // (A per-process cache of device attributes, safe to fill from several host threads at
 // once - they all store the same value; no per-call state.)
@@ -1081,8 +1192,12 @@ hipError_t launch_attention(const sparrow_shape_t &s, const AttnPlan &plan, cons
     if (e != hipSuccess)
         return e;
     const int rows = s.batch * s.num_q_heads;
-    hipLaunchKernelGGL(k_attn_merge, dim3((rows + kMergeRows - 1) / kMergeRows),
-                       dim3(kMergeThreads), 0, stream, a);
+    if (units <= kWideMaxUnits && rows <= kWideMaxRows)
+        hipLaunchKernelGGL(k_attn_merge_wide, dim3((unsigned)rows), dim3(kWideThreads), 0, stream,
+                           a);
+    else
+        hipLaunchKernelGGL(k_attn_merge, dim3((rows + kMergeRows - 1) / kMergeRows),
+                           dim3(kMergeThreads), 0, stream, a);
     return hipGetLastError();
 }
 
