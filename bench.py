@@ -41,14 +41,17 @@ C4_HEADLINE = 2            # index of 10 % in the C4 budget sweep
 # kernels and sources behind each entry point (the counter summaries are tied to them)
 ENTRY = {
     "sparse_attn": ("k_attn_stream<sparse> + k_attn_merge",
-                    ("attention.hip", "common.h", "wave.h")),
-    "dense_attn": ("k_attn_stream<dense> + k_attn_merge", ("attention.hip", "common.h", "wave.h")),
-    "append_score_topk": ("k_page_score (with append) + k_topk",
-                          ("score_topk.hip", "topk.h", "common.h", "wave.h")),
-    "score_topk": ("k_page_score + k_topk", ("score_topk.hip", "topk.h", "common.h", "wave.h")),
-    "decode_step": ("k_page_score (with append) + k_select_attn_unit, or + k_topk + "
-                    "k_attn_stream<sparse> + k_attn_merge",
-                    ("score_topk.hip", "attention.hip", "topk.h", "common.h", "wave.h")),
+                    ("attention.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
+    "dense_attn": ("k_attn_stream<dense> + k_attn_merge",
+                   ("attention.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
+    "append_score_topk": ("k_score_select (with append), or k_page_score + k_topk",
+                          ("score_topk.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
+    "score_topk": ("k_score_select, or k_page_score + k_topk",
+                   ("score_topk.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
+    "decode_step": ("k_decode_unit, or k_page_score (with append) + k_select_attn_unit, or "
+                    "k_score_select + k_attn_stream<sparse> + k_attn_merge",
+                    ("score_topk.hip", "score_unit.h", "attention.hip", "topk.h", "common.h",
+                     "wave.h")),
     "append": ("k_append_kv", ("append.hip", "common.h")),
 }
 
@@ -240,7 +243,7 @@ def acceptance_traffic(workload_name):
     the current source."""
     vals = read_summary(os.path.join(ROOT, "profiles",
                                      "traffic_acceptance_a1_qwen3_vocab_t4096.txt"))
-    if vals.get("source_sha256") != source_sha(("acceptance.hip", "common.h")):
+    if vals.get("source_sha256") != source_sha(("acceptance.hip", "common.h", "wave.h")):
         return None
     v = vals.get(f"traffic_bytes_per_launch[{workload_name}]")
     return None if v is None else float(v)
