@@ -307,8 +307,8 @@ int sparrow_sparse_decode_attn_noalloc(const sparrow_shape_t *shape, const void 
  * out_idx).  Results (caches, meta, out_k, out_idx, out) equal those of the two
  * calls in sequence bit for bit.  When the attention call would run one
  * workgroup per unit (see sparrow_sparse_decode_attn), the selection stays on
- * chip: the whole step is one kernel, or for a few units with long rows the
- * scoring kernel and one for the budget, the top-k and the attention.
+ * chip: the whole step is one kernel, or behind a wide block table the scoring
+ * kernel and one for the budget, the top-k and the attention.
  *
  * Arguments: those of the two calls (k_new and v_new both NULL or both set);
  * workspace of at least sparrow_workspace_size(shape, k_max,

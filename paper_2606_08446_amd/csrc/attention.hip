@@ -793,9 +793,8 @@ __global__ __launch_bounds__(kUnitThreads) void k_select_attn_unit(AttnArgs a, S
 // appended rows from the cache: this workgroup wrote them (the unit's own rows), before the
 // barriers of the selection.  A chain of latencies at this size; against the scoring kernel
 // followed by k_select_attn_unit it saves a launch and the scores' round trip (us per step,
-// 1024-token budget: 8 units x 64 pages 17.5 -> 15.0, 8 x 256 22.1 -> 19.8, 128 x 256 31.3 ->
-// 27.2, 128 x 1024 39.6 -> 37.9, 256 x 1024 55.0 -> 48.3, 128 x 2048 50.5 -> 52.9: the line
-// between the two is score_select_path's).
+// 1024-token budget: 8 units x 64 pages 17.5 -> 15.0, 8 x 256 22.1 -> 19.8, 128 x 256 32.2 ->
+// 28.0, 256 x 512 47.1 -> 40.9), where score_select_path bounds the longest unit.
 template <bool kAppend, bool kMean>
 __global__ __launch_bounds__(kUnitThreads) void k_decode_unit(AttnArgs a, ScoreArgs sa,
                                                               int32_t *__restrict__ out_k,

@@ -11,8 +11,8 @@
 // written as fp32 to the workspace; sequences whose budget covers every page are skipped.
 // A page whose block-table entry lies outside the cache is absent: score 0, nothing read.
 //
-// Most problems run k_score_select instead: one workgroup scores a whole unit (score_unit.h)
-// into LDS and selects from there.  The split pair below serves few units with long rows.
+// Behind narrow block tables k_score_select runs instead: one workgroup scores a whole unit
+// (score_unit.h) into LDS and selects from there.
 //
 // k_topk: one workgroup per (sequence, KV head) - 512 threads, or 256 from 1024 units on -
 // selects the k largest scores with ties to the lower page index.  Scores become
@@ -40,11 +40,13 @@ constexpr int kScoreSmallGrid = 256;  // below this many 32-page workgroups: 8-p
 constexpr int kScoreBatch = 8;   // pages per load batch of a wave
 constexpr int kScoreHeads = 8;   // KV heads per workgroup (at most)
 constexpr int kTopkManyUnits = 1024;  // from this many units on: 256-thread workgroups
-// k_score_select runs 256-thread workgroups from this many units on with at most this many
-// pages (1024 units x 128 pages: 15.0 us against 22.4 with 512 threads, 512 x 512 26.1 against
-// 26.6), else 512-thread ones (1024 x 1170: 114 against 118).
+// k_score_select runs 256-thread workgroups from this many units on (1024 units x 128 pages:
+// 15.0 us against 22.4 with 512 threads, 512 x 512 26.1 against 26.6), else 512-thread ones.
 constexpr int kFusedManyUnits = 512;
-constexpr int kFusedShort = 768;
+// Block-table widths up to which score_select_path takes one workgroup per unit.
+constexpr int kUnitPages = 512;
+constexpr int kUnitPagesFew = 448;
+constexpr int kSplitCheap = 128;  // (below this many units)
 constexpr int kTopkBatch = 8;   // score loads in flight per thread
 
 // One workgroup scores kPages (32, or 8 for small grids) consecutive logical pages of one
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_page_score(
 // it saves over the split scoring is the write of the scores (0.8 % of the bytes, but writes
 // into a saturated read stream cost a tenth of its time), the second launch and the top-k's
 // own load of the scores: a unit's keys never leave LDS, and its selection runs while other
-// units' landmarks stream.
+// units' landmarks stream.  (score_select_path says where it is used.)
 template <bool kAppend, bool kMean, int kThreads>
 __global__ __launch_bounds__(kThreads) void k_score_select(ScoreArgs a,
                                                            int32_t *__restrict__ out_k,
@@ -365,12 +367,20 @@ size_t score_topk_workspace(const sparrow_shape_t &s)
     return (size_t)s.batch * s.num_kv_heads * s.max_pages_per_seq * sizeof(float);
 }
 
-// One workgroup per unit (k_score_select) reads the landmarks no faster than the split kernel,
-// but writes and re-reads no scores and is one launch; the split kernel spreads a unit over the
-// chip, which few units with long rows need.  Selection with the append, both ways, us (units x
-// pages, split / fused): 8 x 64 11.5 / 7.5, 8 x 256 11.8 / 8.9, 8 x 1024 11.7 / 16.6; 128 x 256
-// 13.3 / 9.7, 128 x 1024 21.7 / 19.9, 128 x 4096 54 / 63; 256 x 4096 99 / 87; 512 x 1335 (mean
-// of a ragged batch) 74 / 68; 1024 x 1170 128 / 114; 2048 x 905 182 / 169; 4096 x 157 93 / 70.
+// One workgroup per unit writes and re-reads no scores and is one launch (in a whole step with the
+// attention, k_decode_unit), but it lasts as long as its longest unit, about 13 ns a page whatever
+// the others do, where the split kernel spreads a unit over the chip.  The lengths are not known
+// here, so the line lies where the longest sequence that the block table admits costs no more
+// than the split: 512 pages (four batches for each of the 8 waves), 448 below 128 units, whose
+// split kernels have a cheaper grid.  us, split / one workgroup, selection with the append:
+//   equal lengths, units x pages: 8 x 256 10.4 / 8.8, 8 x 448 10.7 / 10.1, 8 x 512 10.7 / 11.3,
+//     64 x 512 12.5 / 13.2, 128 x 512 17.9 / 13.7, 512 x 512 35.2 / 28.5, 2048 x 512 108 / 96
+//   one sequence of N pages, the others N / 32: 64 units, N = 512 10.7 / 11.4; 128 units, 512
+//     14.6 / 11.4, 1024 15.1 / 17.6; 256 units, 2048 16.2 / 29.7, 4096 23.9 / 53.9; 512 units,
+//     640 15.0 / 16.4; 2048 units, 512 14.7 / 15.0, 1024 15.6 / 18.9, 2048 20.2 / 30.9
+// and for the whole step with a 1024-token budget, N = 1024: 128 units 31.9 / 34.2, 256 33.0 / 35.8.
+// With equal lengths the gain reaches further (256 x 1024 34.1 / 28.7, 2048 x 905 179 / 160), but a
+// table of that width does not say that they are equal.
 // Thousands of units with a handful of pages each are better split (4096 x 13 24 / 31, 16384 x
 // 22 97 / 115, 2048 x 13 equal): their workgroups would be nearly empty.
 bool score_select_path(const sparrow_shape_t &s)
@@ -378,8 +388,7 @@ bool score_select_path(const sparrow_shape_t &s)
     const int64_t units = (int64_t)s.batch * s.num_kv_heads;
     if (units > 2048 && s.max_pages_per_seq < 64)
         return false;
-    return s.max_pages_per_seq <= 512 || units >= 256 ||
-           (units >= 128 && s.max_pages_per_seq <= 2048);
+    return s.max_pages_per_seq <= (units < kSplitCheap ? kUnitPagesFew : kUnitPages);
 }
 
 hipError_t launch_page_score(const sparrow_shape_t &s, const void *q, void *meta,
@@ -449,7 +458,7 @@ hipError_t launch_score_topk(const sparrow_shape_t &s, const void *q, void *meta
                                (size_t)s.max_pages_per_seq * sizeof(uint32_t), stream, a, out_k,
                                out_idx);
         };
-        if (units >= kFusedManyUnits && s.max_pages_per_seq <= kFusedShort)
+        if (units >= kFusedManyUnits)
             go(std::integral_constant<int, 256>{});
         else
             go(std::integral_constant<int, 512>{});

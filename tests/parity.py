@@ -8,6 +8,7 @@ fp64 oracle; metadata bit-exact.
 """
 from __future__ import annotations
 
+import ctypes
 import math
 
 import numpy as np
@@ -25,6 +26,18 @@ SCALE = 1.0 / math.sqrt(128.0)
 
 def log(msg):
     print(msg, flush=True)
+
+
+def _rule(symbol, restype=ctypes.c_bool):
+    f = getattr(S.load(), symbol)
+    f.restype = restype
+    return f
+
+
+def one_workgroup_selection(batch, hkv, max_pages):
+    """The library's rule: whether scoring and selection run in one workgroup per unit."""
+    return _rule("_ZN7sparrow17score_select_pathERK13sparrow_shape")(
+        ctypes.byref(S.make_shape(batch, hkv, hkv, 16, max_pages, 1 << 20)))
 
 
 def gpu_run(inp: W.Inputs, k_max: int, dense=True, out_dtype=S.SPARROW_OUT_F32):
