@@ -706,7 +706,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_stats(
 
 }  // namespace
 
-static int device_cus()
+int device_cus()
 {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

@@ -162,6 +162,9 @@ __device__ __forceinline__ int budget_pages(int L, int ps, const Sched &s, int k
 // ---------------------------------------------------------------------------------------------
 // Launchers (host side, one per kernel family).  All return hipSuccess or the launch error.
 // ---------------------------------------------------------------------------------------------
+// Compute units of the current device (256 where it does not say).
+int device_cus();
+
 hipError_t launch_meta_update(const sparrow_shape_t &s, const void *k_cache,
                               const int32_t *block_table, const int32_t *seq_lens,
                               const int32_t *first_pos, void *meta, hipStream_t stream);

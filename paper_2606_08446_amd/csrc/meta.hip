@@ -13,6 +13,7 @@
 // With the mean landmark the thread instead sums its 8 channels over the page's tokens in
 // token order (fp32 adds of exactly converted bf16 keys) and writes 8 fp32 sums.
 #include "common.h"
+#include "wave.h"
 
 namespace sparrow {
 namespace {
@@ -84,19 +85,22 @@ __device__ __forceinline__ uint32_t unorder16x2(s16x2_t s)
 constexpr int kMinmaxThreads = 512;
 constexpr int kMinmaxWaves = kMinmaxThreads / 64;
 constexpr int kMinmaxRows = 256;  // landmark rows a workgroup holds in LDS (128 KiB)
-constexpr size_t kMinmaxLds = (size_t)kMinmaxRows * 2 * kHeadDim * sizeof(uint16_t);
 constexpr int64_t kMinmaxBytes = 1ll << 30;  // key bytes from which the burst kernel is used
+constexpr int kMinmaxBatch = 4096;  // sequences whose page offsets fit LDS beside the rows
 
-// Min/max landmarks of 16-token pages in large builds, `chunk` (at most 64) pages of a sequence
-// for up to kMinmaxRows / chunk KV heads per workgroup.  Memory-bound, and bound by its writes
-// more than by its reads: landmark rows (512 B per 4 KiB of keys) trickling out between the key
-// reads cost the reads a third of their rate.  So a workgroup keeps its rows in LDS and
-// writes them in one burst of non-temporal stores, as large a burst as LDS takes; with one
-// workgroup per CU the workgroups start together and stay in step well enough that bursts
-// meet bursts.  2.8 GB of keys, 350 MB of landmarks: 632 us with a store after each page,
-// 604 / 589 / 565 with bursts of 32 / 64 / 128 KiB (5.6 TB/s; the larger pages write less:
-// 592 -> 530 us with 32 tokens, but 409 -> 434 where lengths differ 30-fold, and nothing from
-// 64 tokens on, so they stay with k_meta_update).
+// Min/max landmarks of 16-token pages in large builds, one workgroup per CU.  Memory-bound, and
+// bound by its writes more than by its reads: landmark rows (512 B per 4 KiB of keys) trickling
+// out between the key reads cost the reads a third of their rate.  So a workgroup keeps the rows
+// of a chunk of pages (kMinmaxRows rows; one lane per page) in LDS and writes them in one burst
+// of non-temporal stores, and the workgroups, which start together and work alike, stay in step
+// so that bursts meet bursts (the first chunks staggered by halves, quarters or eighths: 3, 5
+// and 6 % slower).  2.7 GB of keys in 64 sequences of 8K-32K tokens: 615 us page by page, 568 so.
+//
+// The batch's pages are laid end to end and every workgroup takes an equal, contiguous share of
+// them, whatever the lengths.  With a workgroup per (sequence, chunk) the empty ones behind a
+// wide block table each waited for a CU of their own, between the full ones: 64 sequences of 300
+// pages behind 2049-page rows 236 us, page by page 131, now 122; 32 of 300 behind 4097 123, 69,
+// 66; 64 of 8 pages behind 2049 12, 34, 7.
 //
 // A wave takes whole (page, head) blocks: a load instruction reads four consecutive key rows
 // (1 KiB), four of them a block, and the next block is in flight while one is folded.  Lane
@@ -104,41 +108,77 @@ constexpr int64_t kMinmaxBytes = 1ll << 30;  // key bytes from which the burst k
 // exchanges join the four row classes.  Rows past the length repeat the last valid one.
 __global__ __launch_bounds__(kMinmaxThreads) void k_meta_minmax(
     const uint16_t *__restrict__ k_cache, const int32_t *__restrict__ block_table,
-    const int32_t *__restrict__ seq_lens, uint16_t *__restrict__ meta, int num_kv_heads,
-    int max_pages, int64_t num_phys, int chunk)
+    const int32_t *__restrict__ seq_lens, uint16_t *__restrict__ meta, int batch,
+    int num_kv_heads, int max_pages, int64_t num_phys, int most)
 {
     constexpr int PS = 16;  // a page is one batch of four loads
-    extern __shared__ u32x4_t s_out[];  // [chunk][heads][32]
-    const int b = blockIdx.y;
-    const int h0 = blockIdx.z * (kMinmaxRows / chunk);
-    const int nh = min(kMinmaxRows / chunk, num_kv_heads - h0);
+    extern __shared__ u32x4_t s_out[];  // [most][heads][32], then the page offsets
+    int32_t *s_off = reinterpret_cast<int32_t *>(s_out + kMinmaxRows * 32);  // [batch + 1]
+    __shared__ int32_t s_scan[kMinmaxWaves];
+    const int h0 = blockIdx.y * (kMinmaxRows / most);
+    const int nh = min(kMinmaxRows / most, num_kv_heads - h0);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int r = lane >> 4;
     const int c = lane & 15;
-    const int32_t *bt = block_table + (int64_t)b * max_pages;
-    const int p0 = blockIdx.x * chunk;
-    // lane i: physical page of page p0 + i, or -1 (absent); requested beside the length
-    int e = bt[p0 + lane < max_pages ? p0 + lane : max_pages - 1];
-    e = e >= 0 && e < num_phys ? e : -1;
-    const int L = clamp_len(seq_lens[b], PS, max_pages);
-    const int n = (L + PS - 1) / PS;
-    if (p0 >= n)
+
+    // ---- page offsets of the sequences, each thread scanning its own few
+    const int per = (batch + kMinmaxThreads - 1) / kMinmaxThreads;
+    const int b0 = min(batch, (int)threadIdx.x * per);
+    const int b1 = min(batch, b0 + per);
+    int mine = 0;
+    for (int b = b0; b < b1; ++b) {
+        s_off[b] = mine;
+        mine += (clamp_len(seq_lens[b], PS, max_pages) + PS - 1) / PS;
+    }
+    const int incl = (int)wave_scan_add((uint32_t)mine);
+    if (lane == 63)
+        s_scan[wave] = incl;
+    __syncthreads();
+    int before = incl - mine;
+    for (int w = 0; w < wave; ++w)
+        before += s_scan[w];
+    for (int b = b0; b < b1; ++b)
+        s_off[b] += before;
+    if (threadIdx.x == kMinmaxThreads - 1)
+        s_off[batch] = before + mine;
+    __syncthreads();
+
+    // ---- this workgroup's pages [lo, hi), `most` at a time
+    const int64_t total = __builtin_amdgcn_readfirstlane(s_off[batch]);
+    const int lo = (int)(total * blockIdx.x / gridDim.x);
+    const int hi = (int)(total * (blockIdx.x + 1) / gridDim.x);
+    if (lo == hi)
         return;
-    const int items = min(chunk, n - p0) * nh;  // (page, head) blocks, page-major
-    const int steps = (items - wave + kMinmaxWaves - 1) / kMinmaxWaves;
-    auto issue = [&](int s, u32x4_t (&v)[4]) {  // s < steps: the page lies inside the sequence
+    // lane i: the physical page of page p0 + i, or -1 (absent), and its valid tokens
+    auto locate = [&](int p0, int &phys, int &valid) {
+        const int f = min(p0 + lane, hi - 1);
+        int b = 0;  // the sequence with s_off[b] <= f < s_off[b + 1]
+        for (int end = batch; end - b > 1;) {
+            const int mid = (b + end) >> 1;
+            if (s_off[mid] <= f)
+                b = mid;
+            else
+                end = mid;
+        }
+        const int page = f - s_off[b];
+        const int e = block_table[(int64_t)b * max_pages + page];
+        phys = e >= 0 && e < num_phys ? e : -1;
+        valid = min(PS, clamp_len(seq_lens[b], PS, max_pages) - page * PS);
+    };
+    int phys, valid;
+    auto issue = [&](int s, u32x4_t (&v)[4]) {
         const int it = wave + kMinmaxWaves * s;
         const int pg = it / nh;
         const int h = h0 + it - pg * nh;
-        const int ph = __builtin_amdgcn_readlane(e, pg);
-        const int valid = min(PS, L - (p0 + pg) * PS);
+        const int ph = __builtin_amdgcn_readlane(phys, pg);
+        const int rows = __builtin_amdgcn_readlane(valid, pg);
         const uint16_t *src =  // (an absent page reads page 0)
             k_cache + ((int64_t)(ph < 0 ? 0 : ph) * num_kv_heads + h) * PS * kHeadDim + 8 * c;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int row = 4 * j + r;
-            v[j] = ld16_nt(src + (row < valid ? row : valid - 1) * kHeadDim);
+            v[j] = ld16_nt(src + (row < rows ? row : rows - 1) * kHeadDim);
         }
     };
     auto fold = [&](int s, const u32x4_t (&v)[4]) {
@@ -159,41 +199,63 @@ __global__ __launch_bounds__(kMinmaxThreads) void k_meta_minmax(
         for (int w = 0; w < 4; ++w) {
 #pragma unroll
             for (int x = 16; x < 64; x <<= 1) {
-                const int lo = __shfl_xor(__builtin_bit_cast(int, mn[w]), x, 64);
-                const int hi = __shfl_xor(__builtin_bit_cast(int, mx[w]), x, 64);
-                mn[w] = __builtin_elementwise_min(mn[w], __builtin_bit_cast(s16x2_t, lo));
-                mx[w] = __builtin_elementwise_max(mx[w], __builtin_bit_cast(s16x2_t, hi));
+                const int lo16 = __shfl_xor(__builtin_bit_cast(int, mn[w]), x, 64);
+                const int hi16 = __shfl_xor(__builtin_bit_cast(int, mx[w]), x, 64);
+                mn[w] = __builtin_elementwise_min(mn[w], __builtin_bit_cast(s16x2_t, lo16));
+                mx[w] = __builtin_elementwise_max(mx[w], __builtin_bit_cast(s16x2_t, hi16));
             }
             out[w] = unorder16x2(r & 1 ? mx[w] : mn[w]);
         }
         if (lane < 32)  // lanes 0-15 the min row, 16-31 the max row
             s_out[(wave + kMinmaxWaves * s) * 32 + lane] = out;
     };
+    // (page, head) blocks of the chunk at p0, page-major, and this wave's share of them
+    auto blocks_of = [&](int p0) { return min(most, hi - p0) * nh; };
+    auto steps_of = [&](int items) { return (items - wave + kMinmaxWaves - 1) / kMinmaxWaves; };
+
+    locate(lo, phys, valid);
+    int items = blocks_of(lo);
+    int steps = steps_of(items);
     u32x4_t nxt[4];
     if (steps > 0)
         issue(0, nxt);
-    int s = 0;
-    for (; s + 1 < steps; ++s) {
-        u32x4_t cur[4];
+    for (int p0 = lo; p0 < hi; p0 += most) {
+        const bool more = p0 + most < hi;
+        int phys2 = -1, valid2 = 1;
+        if (more)
+            locate(p0 + most, phys2, valid2);
+        int s = 0;
+        for (; s + 1 < steps; ++s) {
+            u32x4_t cur[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            cur[j] = nxt[j];
-        issue(s + 1, nxt);
-        fold(s, cur);
-    }
-    if (s < steps)
-        fold(s, nxt);
-    __syncthreads();
-    // the burst: a wave writes two landmark rows (1 KiB) per instruction (every lane takes part
-    // in the exchange of the page's entry, also past the last row)
-    for (int it0 = 2 * wave; it0 < items; it0 += 2 * kMinmaxWaves) {
-        const int it = it0 + (lane >> 5);
-        const int pg = (it < items ? it : items - 1) / nh;
-        const int ph = __shfl(e, pg, 64);
-        if (it < items && ph >= 0)
-            __builtin_nontemporal_store(s_out[it * 32 + (lane & 31)],
-                                        reinterpret_cast<u32x4_t *>(meta) + (lane & 31) +
-                                            ((int64_t)ph * num_kv_heads + h0 + it - pg * nh) * 32);
+            for (int j = 0; j < 4; ++j)
+                cur[j] = nxt[j];
+            issue(s + 1, nxt);
+            fold(s, cur);
+        }
+        if (s < steps)
+            fold(s, nxt);
+        __syncthreads();
+        // the burst: a wave writes two landmark rows (1 KiB) per instruction (every lane takes
+        // part in the exchange of the page's entry, also past the last row)
+        for (int it0 = 2 * wave; it0 < items; it0 += 2 * kMinmaxWaves) {
+            const int it = it0 + (lane >> 5);
+            const int pg = (it < items ? it : items - 1) / nh;
+            const int ph = __shfl(phys, pg, 64);
+            if (it < items && ph >= 0)
+                __builtin_nontemporal_store(s_out[it * 32 + (lane & 31)],
+                                            reinterpret_cast<u32x4_t *>(meta) + (lane & 31) +
+                                                ((int64_t)ph * num_kv_heads + h0 + it - pg * nh) * 32);
+        }
+        if (more) {  // (its first loads behind this wave's stores: before them costs 1 %)
+            phys = phys2;
+            valid = valid2;
+            items = blocks_of(p0 + most);
+            steps = steps_of(items);
+            if (steps > 0)
+                issue(0, nxt);
+        }
+        __syncthreads();  // the rows are out of LDS before the next chunk's arrive
     }
 }
 
@@ -278,20 +340,21 @@ hipError_t launch_ps(const sparrow_shape_t &s, const void *k_cache, const int32_
 {
     const int rebuild = first_pos == nullptr;
     const int64_t page_bytes = (int64_t)s.num_kv_heads * PS * kHeadDim * 2;
-    // A large build by bursts.  Below about 1 GiB of keys the shorter chain of the
-    // page-per-workgroup kernel wins: one 4096-token sequence 9.5 us against 10.7, 16
-    // sequences of 4K-24K tokens (0.9 GB) 90.5 us either way.
+    // A large build by bursts: never slower from 1 GiB of possible keys on.  Below it the shorter
+    // chain of the page-per-workgroup kernel can be: one sequence of 1000 pages 7.6 us against
+    // 8.2, 4 of 250 7.9 against 9.4, 64 of 30 13.6 against 15.7.
     if (PS == 16 && rebuild && s.landmark == SPARROW_LANDMARK_MINMAX &&
-        page_bytes * s.max_pages_per_seq * s.batch >= kMinmaxBytes) {
-        int chunk = kMinmaxRows / (s.num_kv_heads < kMinmaxRows ? s.num_kv_heads : kMinmaxRows);
-        chunk = chunk < 64 ? chunk : 64;  // one lane per page
-        const int heads = kMinmaxRows / chunk;  // per workgroup
-        const dim3 grid((s.max_pages_per_seq + chunk - 1) / chunk, s.batch,
-                        (s.num_kv_heads + heads - 1) / heads);
-        hipLaunchKernelGGL(k_meta_minmax, grid, dim3(kMinmaxThreads), kMinmaxLds, st,
+        s.batch <= kMinmaxBatch && page_bytes * s.max_pages_per_seq * s.batch >= kMinmaxBytes) {
+        int most = kMinmaxRows / (s.num_kv_heads < kMinmaxRows ? s.num_kv_heads : kMinmaxRows);
+        most = most < 64 ? most : 64;  // one lane per page
+        const int heads = kMinmaxRows / most;  // per workgroup
+        const dim3 grid(device_cus(), (s.num_kv_heads + heads - 1) / heads);
+        const size_t lds = (size_t)kMinmaxRows * 2 * kHeadDim * sizeof(uint16_t) +
+                           (size_t)(s.batch + 1) * sizeof(int32_t);
+        hipLaunchKernelGGL(k_meta_minmax, grid, dim3(kMinmaxThreads), lds, st,
                            static_cast<const uint16_t *>(k_cache), bt, lens,
-                           static_cast<uint16_t *>(meta), s.num_kv_heads, s.max_pages_per_seq,
-                           s.num_phys_pages, chunk);
+                           static_cast<uint16_t *>(meta), s.batch, s.num_kv_heads,
+                           s.max_pages_per_seq, s.num_phys_pages, most);
         return hipGetLastError();
     }
     const dim3 grid = rebuild ? dim3(s.max_pages_per_seq, s.batch) : dim3(s.batch);
