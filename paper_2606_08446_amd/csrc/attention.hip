@@ -43,8 +43,11 @@ constexpr int kAttnThreads = 256;
 constexpr int kAttnWaves = kAttnThreads / 64;
 constexpr int kBatch = 64;        // pages per prefetched page-list batch
 constexpr int kMaxWaves = 4096;   // upper bound of streaming waves (sizes the workspace)
-constexpr int kUnitSegments = 256;  // streaming waves per (sequence, KV head) unit, on average
-constexpr int kFineSegments = 128;  // and up to which a wave may have a single 16-token chunk
+// Streaming waves per (sequence, KV head) unit, on average: at most, and up to which a wave may
+// have a single 16-token chunk (with at most kFewRows query-head rows in the batch, else half).
+constexpr int kUnitSegments = 256;
+constexpr int kFineSegments = 128;
+constexpr int kFewRows = 32;
 
 struct AttnArgs {
     const uint16_t *q;
@@ -59,7 +62,8 @@ struct AttnArgs {
     float *o_part;
     float *ml_part;
     void *out;
-    int k_max, batch, num_q_heads, num_kv_heads, ps, max_pages, out_bf16, total_waves;
+    int k_max, batch, num_q_heads, num_kv_heads, ps, max_pages, out_bf16;
+    int max_waves, fine_waves;  // streaming waves at most; and with single chunks (see k_attn_stream)
     int64_t num_phys;  // physical pages in the caches
     float scale_log2;
 };
@@ -281,18 +285,20 @@ __global__ __launch_bounds__(kAttnThreads) void k_attn_stream(AttnArgs a)
 
     const int64_t P = (int64_t)s_off[B] * Hkv;
     // One wave per listed page at most, and on average at most kUnitSegments waves per unit, or
-    // kFineSegments where a wave would have less than two 16-token chunks: the merge reads
-    // one partial per wave, and its time has to stay small against what more waves save.
-    // Kernel times of a dense call with caps of 64 / 128 / 256 / 512, attention + merge in us:
-    // 8 units x 4096 tokens 9.6+3.9 / 7.3+4.9 / 7.2+6.1 / 7.2+5.5, 8 x 16384 27.2+4.6 /
+    // half or all of kFineSegments where a wave would have less than two 16-token chunks: the
+    // merge reads one partial per wave, and its time has to stay small against what more waves
+    // save.  Kernel times of a dense call with caps of 64 / 128 / 256 / 512, attention + merge in
+    // us: 8 units x 4096 tokens 9.6+3.9 / 7.3+4.9 / 7.2+6.1 / 7.2+5.5, 8 x 16384 27.2+4.6 /
     // 17.9+4.4 / 15.8+5.5 / 15.9+5.5, 8 x 65536 (5 heads each) 99+4.6 / 55.9+4.9 / 45.4+6.1 /
-    // 45.4+6.0, 2 x 16384 25.6+4.6 / 16.1+4.7 / 11.1+6.2 / 9.4+9.2.
-    const int64_t units = (int64_t)B * Hkv;
-    int64_t W = P < a.total_waves ? P : a.total_waves;
-    const int64_t pairs = P * (a.ps >> 4) / 2;
-    const int64_t fine = units * kFineSegments > pairs ? units * kFineSegments : pairs;
-    W = W < fine ? W : fine;
-    W = W < units * kUnitSegments ? W : units * kUnitSegments;
+    // 45.4+6.0, 2 x 16384 25.6+4.6 / 16.1+4.7 / 11.1+6.2 / 9.4+9.2.  A partial holds a row per
+    // query head, so single chunks pay for few rows only: dense calls of 2048 tokens, 64 / 128 waves
+    // of one or two chunks, us: 8 units x 2 heads 11.3 / 10.3, 8 x 4 11.2 / 10.8, 4 x 8 11.0 /
+    // 10.9, 8 x 16 13.6 / 15.5, 16 x 4 12.1 / 12.9, 16 x 16 17.1 / 22.8 (21.2 with the
+    // half-wave merge).
+    int64_t W = P * (a.ps >> 4) / 2;
+    W = W > a.fine_waves ? W : a.fine_waves;
+    W = W < a.max_waves ? W : a.max_waves;
+    W = W < P ? W : P;
     const int w = blockIdx.x * kAttnWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w >= W)
         return;
@@ -946,12 +952,13 @@ __global__ __launch_bounds__(kMergeThreads) void k_attn_merge(AttnArgs a)
     store_out4(a.out, a.out_bf16, orow, acc * inv);
 }
 
-// The same merge for few units, whose lists are spread over many waves (up to kUnitSegments and
-// one more, or two, each): one workgroup per query-head row.  k_attn_merge is a chain there, one
-// round trip to memory per 16 partials of a row, with two workgroups on the whole chip; here
-// every half-wave takes kWideChunk partials at a time, so 16 half-waves have 128 of them in
-// flight, and the half-waves' (m, l, o) states meet in LDS.  It is bound by the latency of its
-// launch and two dependent round trips.
+// The same merge for few units, whose lists are spread over many waves: kUnitSegments each at
+// most where the lists are equal, nearly all of the launch's waves for one long list among short
+// ones.  One workgroup per query-head row.  k_attn_merge is a chain there, one round trip to memory per 16
+// partials of a row, with two workgroups on the whole chip; here every half-wave takes kWideChunk
+// partials at a time, so 16 half-waves have 128 of them in flight, and the half-waves' (m, l, o)
+// states meet in LDS.  Equal lists take its launch and two or three dependent round trips, 2000
+// partials of one unit 16.
 constexpr int kWideThreads = 512;
 constexpr int kWideParts = kWideThreads / 32;
 constexpr int kWideChunk = 8;
@@ -1145,7 +1152,11 @@ AttnArgs make_args(const sparrow_shape_t &s, const AttnPlan &plan, const void *q
     a.max_pages = s.max_pages_per_seq;
     a.num_phys = s.num_phys_pages;
     a.out_bf16 = out_dtype == SPARROW_OUT_BF16 ? 1 : 0;
-    a.total_waves = device_waves();
+    const int64_t units = (int64_t)s.batch * s.num_kv_heads;
+    const int fine = s.batch * s.num_q_heads <= kFewRows ? kFineSegments : kFineSegments / 2;
+    const int64_t waves = device_waves();
+    a.max_waves = (int)(units * kUnitSegments < waves ? units * kUnitSegments : waves);
+    a.fine_waves = (int)(units * fine < waves ? units * fine : waves);
     a.scale_log2 = scale * 1.4426950408889634f;
     return a;
 }
@@ -1180,7 +1191,7 @@ hipError_t launch_attention(const sparrow_shape_t &s, const AttnPlan &plan, cons
                                stream, a);
         return hipGetLastError();
     }
-    const dim3 grid(a.total_waves / kAttnWaves);
+    const dim3 grid(device_waves() / kAttnWaves);
     if (idx != nullptr)
         hipLaunchKernelGGL(k_attn_stream<true>, grid, dim3(kAttnThreads), plan.lds_bytes, stream,
                            a);
