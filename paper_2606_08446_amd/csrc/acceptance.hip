@@ -42,6 +42,7 @@ constexpr int kAccThreads = 512;
 constexpr int kAccWaves = kAccThreads / 64;
 constexpr int kAccLdsVecs = 9;  // 16-byte vectors of each row a thread keeps in LDS
 constexpr int kAccBatch = 3;    // vectors of each row a thread has in flight beside the kept ones
+constexpr int kAccFold = 8;     // groups of them after which a thread's partial sums are put aside
 constexpr int kAccSmallVocab = 64;  // rows shorter than this: one wave per token
 constexpr int kTailThreads = 1024;
 constexpr int kTailWaves = kTailThreads / 64;
@@ -340,6 +341,11 @@ __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict_
             lse_add(a, xa, ts);
             lse_add(b, xb, ts);
         }
+        // The sums so far are put aside here and after every kAccFold groups: one sum of all of a
+        // thread's vectors (74 of Qwen3's vocabulary in fp32) would be a chain whose roundings
+        // show where one entry holds most of the mass.
+        Lse pa = a, pb = b;
+        a.s = b.s = 0.f;
         // The other slots roll through na, nb: each is replaced by its successor as soon as it
         // is used, and the last group stays for the second pass, which goes back to front.
         auto first_use = [&](int g, int u) {
@@ -356,12 +362,17 @@ __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict_
                 first_use(g, u);
                 load_loose(x, g + 1, u, kFirst);
             }
+            if ((g + 1) % kAccFold == 0) {
+                pa = lse_merge(pa, a);
+                pb = lse_merge(pb, b);
+                a.s = b.s = 0.f;
+            }
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u)
             first_use(groups - 1, u);
-        a = wave_lse(a);
-        b = wave_lse(b);
+        a = wave_lse(lse_merge(pa, a));
+        b = wave_lse(lse_merge(pb, b));
         if (lane == 0) {
             s_red[round][wave][0] = a;
             s_red[round][wave][1] = b;
@@ -385,7 +396,7 @@ __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict_
 
         // ---- pass 2: sum of 2^min(ts a - P, ts b - Q), the other slots first (the last group
         // is still here), then LDS, then the kept slots, each replaced by the next token's
-        float acc = 0.f;
+        float acc = 0.f, aside = 0.f;  // (put aside as in the first pass)
         if (x.odd)
             acc += exp2_hw(fminf(fmaf(ts, x.oa, -P), fmaf(ts, x.ob, -Q)));
         auto second_use = [&](int g, int u) {
@@ -399,6 +410,10 @@ __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict_
                     second_use(g, u);
                     load_loose(x, g - 1, u, kAgain);
                 }
+                if (g % kAccFold == 0) {
+                    aside += acc;
+                    acc = 0.f;
+                }
             }
 #pragma unroll
             for (int u = 0; u < NB; ++u)
@@ -409,6 +424,8 @@ __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict_
             if (x.has(u))
                 acc += min_sum_vec<T, kNeg>(s_keep[u * kAccThreads + tid],
                                             s_keep[(L + u) * kAccThreads + tid], ts, P, Q);
+        aside += acc;
+        acc = 0.f;
         const int64_t tn = (int64_t)t + gridDim.x;
         const bool more = tn < tokens;
         RowPair<T, kNeg> y = x;
@@ -429,7 +446,7 @@ __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict_
                 if (x.has(L + j))
                     acc += min_sum_vec<T, kNeg>(ka[j], kb[j], ts, P, Q);
         }
-        acc = wave_sum_f(acc) * rounding_factor(lp, lq);
+        acc = wave_sum_f(acc + aside) * rounding_factor(lp, lq);
         if (lane == 0)
             s_sum[round][wave] = acc;
         if (!more)

@@ -11,6 +11,8 @@ import torch
 import oracle
 from paper_2606_08446_amd import sparrow as S
 
+from parity import log
+
 pytestmark = pytest.mark.gpu
 
 # fp32 sums of up to 150000 terms over 512 threads and the exponents' rounding (2^-22 for terms
@@ -60,3 +62,29 @@ def test_several_tokens_per_workgroup(gpu_device, dtype, V):
 @pytest.mark.parametrize("dtype,V", [("f32", 63001), ("bf16", 125003)])
 def test_long_rows_several_tokens(gpu_device, dtype, V):
     check(300, V, dtype, V, jump=True, tau=-0.3 if dtype == "f32" else 1.0)
+
+
+# One entry holds nearly all of the target's mass, and a vector of the others (w entries) adds
+# less than half a unit of that entry's partial sum, so it is lost there: a chain of 24 vectors
+# leaves the row's sum 24 w t short, t the others' size, and the rate here, the sum of the
+# others under a flat draft row, is off by as much of itself.  (One chain of a thread's 122
+# fp32 or 61 bf16 vectors: 6.3e-6, 3.1e-6.)  The partial sums and the sums over a wave and
+# the workgroup add that entry to others 6 + 6 + 7 times, rounded to 2^-24 each.  The draft's
+# values make its log-sum-exp nearly 0, with no rounding to share.
+@pytest.mark.parametrize("dtype,value,flat,w", [("f32", -18.16, -12.4292, 4),
+                                                ("bf16", -18.875, -12.4375, 8)])
+def test_partial_sums_stay_short(gpu_device, dtype, value, flat, w):
+    V, T = 250000, 40
+    t = np.exp(value)
+    assert w * t < 2.0 ** -24
+    a = np.full((T, V), value, np.float32)
+    at = np.linspace(0, V - 1, T).astype(np.int64)   # in LDS, in registers, read again
+    a[np.arange(T), at] = 0
+    b = np.full((T, V), flat, np.float32)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, y = torch.from_numpy(a).to(dt), torch.from_numpy(b).to(dt)
+    got = S.acceptance_rate(x.cuda(), y.cuda()).cpu().numpy().astype(np.float64)
+    want = oracle.acceptance(x.float().numpy(), y.float().numpy(), 1.0)
+    err = np.abs(got / want - 1)
+    log(f"case partial sums {dtype}: {err.max():.2e}")
+    assert err.max() <= 24 * w * t + 19 * 2.0 ** -24, err.max()
