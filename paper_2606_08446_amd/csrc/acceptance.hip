@@ -9,7 +9,8 @@
 // between the passes: 144 KiB in LDS, 21 (fp32) or 19 (bf16) vectors per thread and row in
 // registers - 40 % of an fp32 row pair of Qwen3's vocabulary, three quarters of a bf16 one.
 // The rest is read again, last part first, while the L2 may still hold it; where there is a
-// rest, the kept vectors are read non-temporally to leave the caches to it.
+// rest and more than a few tokens, the kept vectors are read non-temporally to leave the caches
+// to it.
 //
 // What bounds it: fp32 rows their traffic (1.5 times the rows, at 7.5 TB/s), bf16 rows the
 // arithmetic and the turns between the passes.  With one token per workgroup the memory was
@@ -279,7 +280,7 @@ struct RowPair {
     }
 };
 
-template <typename T, bool kNeg, bool kLong>
+template <typename T, bool kNeg, bool kOnce>
 __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict__ target,
                                                             const T *__restrict__ draft, int tokens,
                                                             int V, float ts,
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(kAccThreads) void k_acceptance(const T *__restrict_
         r.template load<decltype(again)::value>(slot_of(g, u), na[u], nb[u]);
     };
     auto load_kept = [&](const RowPair<T, kNeg> &r, int j) {
-        r.template load<kLong>(L + j, ka[j], kb[j]);
+        r.template load<kOnce>(L + j, ka[j], kb[j]);
     };
     constexpr std::false_type kFirst{};
     constexpr std::true_type kAgain{};
@@ -748,11 +749,16 @@ hipError_t launch_acceptance(int64_t T, int V, int dtype, const void *target, co
                                dim3((unsigned)T), dim3(64), 0, stream, p, q, V, ts, alpha);
             return;
         }
-        const bool fits =
-            V / Logit<L>::kVec <= (Logit<L>::kKeep + kAccLdsVecs) * kAccThreads;
-        auto kernel = fits ? (neg ? k_acceptance<L, true, false> : k_acceptance<L, false, false>)
-                           : (neg ? k_acceptance<L, true, true> : k_acceptance<L, false, true>);
+        // Non-temporal loads of the kept vectors leave the caches to the others, which are read
+        // again; a few tokens find all of theirs in the caches.  fp32, plain / non-temporal, us:
+        // 16 tokens of 62000 entries 16.1 / 19.1, 16 of 151936 33.0 / 35.5, 64 of 65536 17.8 /
+        // 20.2, 64 of 151936 42.2 / 40.5, 128 of 80000 28.1 / 26.5, 256 of 131072 65.4 / 60.4;
+        // bf16 16 of 151936 28.6 / 30.4, 128 of 131072 29.8 / 29.6, 256 39.1 / 38.1.
         const int cus = device_cus();
+        const bool once = T >= cus / 2 &&
+                          V / Logit<L>::kVec > (Logit<L>::kKeep + kAccLdsVecs) * kAccThreads;
+        auto kernel = once ? (neg ? k_acceptance<L, true, true> : k_acceptance<L, false, true>)
+                           : (neg ? k_acceptance<L, true, false> : k_acceptance<L, false, false>);
         hipLaunchKernelGGL(kernel, dim3((unsigned)(T < cus ? T : cus)), dim3(kAccThreads), kKeep,
                            stream, p, q, (int)T, V, ts, alpha);
     };
