@@ -541,14 +541,14 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_stats(
     int n_bins, double pct, double *__restrict__ quantile, double *__restrict__ mean,
     int64_t *__restrict__ count)
 {
-    __shared__ uint32_t hist[2][256];
+    __shared__ unsigned long long hist[2][256];  // (a bin may hold more than 2^32 tokens)
     __shared__ double s_sum[kTailWaves];
     __shared__ unsigned long long s_cnt[kTailWaves];
     __shared__ uint32_t s_min[kTailWaves], s_max[kTailWaves];
     __shared__ uint32_t s_first[kTailWaves], s_above[kTailWaves];
     __shared__ uint32_t s_digit;
     __shared__ int64_t s_rank;
-    __shared__ uint32_t s_in_digit;
+    __shared__ int64_t s_in_digit;
     const int bin = blockIdx.x;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_stats(
         s_max[wave] = kmax;
     }
     if (tid < 256)
-        hist[0][tid] = 0u;
+        hist[0][tid] = 0;
     __syncthreads();
     double total = 0.0;
     int64_t N = 0;
@@ -638,20 +638,20 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_stats(
         each([&](float v) {
             const uint32_t key = float_key(v);
             if ((key & ~mask) == prefix)
-                atomicAdd(&hist[cur][(key & mask) >> shift], 1u);
+                atomicAdd(&hist[cur][(key & mask) >> shift], 1ull);
         });
         if (tid < 256)
-            hist[cur ^ 1][tid] = 0u;
+            hist[cur ^ 1][tid] = 0;
         __syncthreads();
         if (wave == 0) {  // lane l owns digits 4l .. 4l + 3
-            uint32_t c[4];
+            int64_t c[4];
             int64_t before = 0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                c[i] = hist[cur][4 * lane + i];
+                c[i] = (int64_t)hist[cur][4 * lane + i];
                 before += c[i];
             }
-            const int64_t own = before;  // (64-bit: a bin may hold more than 2^32 tokens)
+            const int64_t own = before;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 const int64_t up = __shfl_up((long long)before, o, 64);
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_stats(
             before -= own;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if (rank >= before && rank < before + (int64_t)c[i]) {
+                if (rank >= before && rank < before + c[i]) {
                     s_digit = 4 * lane + i;
                     s_rank = rank - before;
                     s_in_digit = c[i];

@@ -40,3 +40,22 @@ def test_tail_edges(gpu_device, T, kind):
         # (another order of at most 20001 fp64 additions)
         size = np.abs(alpha.astype(np.float64)).max()
         np.testing.assert_allclose(m.cpu().numpy()[ok], rm[ok], rtol=0, atol=20001 * 2.0**-53 * size)
+
+
+def test_more_tokens_than_32_bits_count(gpu_device):
+    """One bin of 2^32 + 11 tokens (34 GB), all but five with one key: a digit's count does not
+    fit 32 bits.  The keys differ in the lowest bit only, so one pass decides the rank."""
+    T = 2 ** 32 + 11
+    if torch.cuda.mem_get_info(gpu_device)[0] < 10 * T:
+        pytest.skip("needs 40 GB of free device memory")
+    low, high = np.array([0x3f400000, 0x3f400001], np.uint32).view(np.float32)
+    alpha = torch.full((T,), float(high), dtype=torch.float32, device=gpu_device)
+    alpha[:5] = float(low)
+    pos = torch.zeros(T, dtype=torch.int32, device=gpu_device)
+    torch.cuda.synchronize()
+    q, m, c = (x.cpu().numpy() for x in S.tail_stats(alpha, pos, 64, 1, 50.0))
+    assert c[0] == T
+    assert q[0] == np.float64(high)
+    assert low < m[0] <= high
+    del alpha, pos
+    torch.cuda.empty_cache()
