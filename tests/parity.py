@@ -9,6 +9,7 @@ fp64 oracle; metadata bit-exact.
 from __future__ import annotations
 
 import ctypes
+import dataclasses
 import math
 
 import numpy as np
@@ -38,6 +39,19 @@ def one_workgroup_selection(batch, hkv, max_pages):
     """The library's rule: whether scoring and selection run in one workgroup per unit."""
     return _rule("_ZN7sparrow17score_select_pathERK13sparrow_shape")(
         ctypes.byref(S.make_shape(batch, hkv, hkv, 16, max_pages, 1 << 20)))
+
+
+def widen(inp: W.Inputs, own_pages=False) -> W.Inputs:
+    """The same sequences behind a block table too wide for one workgroup per unit, so that they
+    take the split scoring and top-k kernels.  The further columns lie outside the cache, or
+    with own_pages repeat the sequence's first page (for lengths that reach them)."""
+    B, M = inp.block_table.shape
+    bt = torch.full((B, max(M, 520)), 1 << 30, dtype=torch.int32, device=inp.block_table.device)
+    if own_pages:
+        bt[:] = inp.block_table[:, :1]
+    bt[:, :M] = inp.block_table
+    assert not one_workgroup_selection(B, inp.workload.num_kv_heads, bt.shape[1])
+    return dataclasses.replace(inp, block_table=bt)
 
 
 def gpu_run(inp: W.Inputs, k_max: int, dense=True, out_dtype=S.SPARROW_OUT_F32):

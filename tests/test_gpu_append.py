@@ -11,7 +11,7 @@ from paper_2606_08446_amd import sparrow as S
 from paper_2606_08446_amd import workloads as W
 
 from parity import (SCALE, check_indices, check_out, host, log, oracle_budgets,
-                    sample_inputs)
+                    sample_inputs, widen)
 
 pytestmark = pytest.mark.gpu
 
@@ -32,14 +32,16 @@ def new_rows(B, Hkv, seed):
     return k, v
 
 
-def append_case(G, Hkv, ps, lengths, seed, schedule=None, skip_last=True):
+def append_case(G, Hkv, ps, lengths, seed, schedule=None, skip_last=True, wide=False):
     """Inputs whose seq_lens count the token to append, and metadata (from the oracle) that
     describes the tokens before it.  With skip_last, the longest sequence gets a length one
-    past what the block table addresses (the append must leave it alone)."""
+    past what the block table addresses (the append must leave it alone).  `wide`: behind a
+    block table that takes the split scoring."""
     schedule = schedule or W.fraction_budget(1, 4)
     w = W.small(B=len(lengths), Hq=G * Hkv, Hkv=Hkv, ps=ps, lengths=lengths, seed=seed,
                 schedule=schedule)
     inp = W.generate(w, DEV, lengths=list(lengths))
+    inp = widen(inp, own_pages=True) if wide else inp
     lens = np.asarray(lengths, np.int32).copy()
     if skip_last:
         b = int(np.argmax(lens))
@@ -108,16 +110,18 @@ def clone_inputs(inp):
     return c
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("case", range(len(CASES)))
-def test_fused_equals_append_then_select(case):
+def test_fused_equals_append_then_select(case, wide):
     G, Hkv, ps, lengths = CASES[case]
-    log(f"case fused G={G} Hkv={Hkv} ps={ps} lengths={lengths}")
+    log(f"case fused G={G} Hkv={Hkv} ps={ps} lengths={lengths} wide={wide}")
     # a quarter of the pages with a floor of 2 pages: short sequences are dense (k = n)
-    fused_check(G, Hkv, ps, lengths, 60 + case, W.Schedule(1 << 20, (2,), (1,), 4))
+    fused_check(G, Hkv, ps, lengths, 60 + case, W.Schedule(1 << 20, (2,), (1,), 4), wide=wide)
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("seed", range(8))
-def test_fused_random_shapes(seed):
+def test_fused_random_shapes(seed, wide):
     rng = np.random.default_rng(5000 + seed)
     G = int(rng.choice([1, 2, 4, 5, 8]))
     Hkv = int(rng.integers(1, 11))
@@ -127,26 +131,28 @@ def test_fused_random_shapes(seed):
     lengths[int(rng.integers(0, B))] = int(rng.choice([1, ps, ps + 1, 2 * ps]))
     sched = W.fraction_budget(int(rng.integers(1, 4)), int(rng.integers(4, 12)),
                               floor_pages=int(rng.integers(0, 4)))
-    log(f"case fused random {seed}: G={G} Hkv={Hkv} ps={ps} lengths={lengths}")
-    fused_check(G, Hkv, ps, tuple(lengths), 5100 + seed, sched, skip_last=seed % 2 == 0)
+    log(f"case fused random {seed}: G={G} Hkv={Hkv} ps={ps} lengths={lengths} wide={wide}")
+    fused_check(G, Hkv, ps, tuple(lengths), 5100 + seed, sched, skip_last=seed % 2 == 0, wide=wide)
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("G,n_bins", [(16, 256), (12, 300)])
-def test_fused_large_groups_and_many_bins(G, n_bins):
+def test_fused_large_groups_and_many_bins(G, n_bins, wide):
     # more than 8 query heads per KV head (a second batch of query rows in the scoring
-    # prologue) and schedule tables staged in LDS (256 bins) or read from memory (300)
+    # prologue) and schedule tables that the split scoring stages in LDS (256 bins) or reads
+    # from memory (300)
     rng = np.random.default_rng(77 + n_bins)
     sched = W.Schedule(16, tuple(int(x) for x in rng.integers(0, 7, n_bins)),
                        tuple(int(x) for x in rng.integers(1, 10, n_bins)), 20)
-    log(f"case fused G={G} with {n_bins} schedule bins")
-    fused_check(G, 2, 16, (3000, 4097, 6000, 5), 90 + G, sched)
+    log(f"case fused G={G} with {n_bins} schedule bins wide={wide}")
+    fused_check(G, 2, 16, (3000, 4097, 6000, 5), 90 + G, sched, wide=wide)
 
 
-def fused_check(G, Hkv, ps, lengths, seed, schedule, skip_last=True):
+def fused_check(G, Hkv, ps, lengths, seed, schedule, skip_last=True, wide=False):
     """The fused append + selection equals the append followed by the selection bit for
     bit, and both match the oracle through attention."""
     inp, meta, meta0, kn, vn = append_case(G, Hkv, ps, lengths, seed=seed, schedule=schedule,
-                                           skip_last=skip_last)
+                                           skip_last=skip_last, wide=wide)
     k_max = inp.max_pages
     a = clone_inputs(inp)
     meta_a = meta.clone()

@@ -4,8 +4,9 @@ It must give, bit for bit, what sparrow_append_score_topk (or sparrow_page_score
 no token is appended) followed by sparrow_sparse_decode_attn gives on the same inputs:
 caches, metadata, budgets, page lists and outputs.  The cases sit on both sides of the
 attention's one-workgroup-per-unit switch (at most 256 units, G <= 8, k_max * page_size <=
-1024 and a block table of at most 4096 pages), where the step runs the budget, the top-k and
-the attention in one kernel after the scoring kernel; they cover forced sink/local pages,
+1024 and a block table of at most 4096 pages).  There the step is one kernel behind a narrow
+block table, and behind a wide one (`wide`) the scoring kernel and one for the budget, the
+top-k and the attention; they cover forced sink/local pages,
 schedule tables too long to stage on chip, the mean-key landmark, bf16 output, empty and
 one-token sequences and capped budgets.  One case is checked against the CPU oracle as well.
 """
@@ -17,7 +18,7 @@ import oracle
 from paper_2606_08446_amd import sparrow as S
 from paper_2606_08446_amd import workloads as W
 
-from parity import SCALE, check_indices, check_out, host, log
+from parity import SCALE, check_indices, check_out, host, log, one_workgroup_selection, widen
 from test_gpu_append import append_case, clone_inputs
 
 pytestmark = pytest.mark.gpu
@@ -135,16 +136,22 @@ CASES = [
     (2, 8, 16, (4096, 1000, 513, 1, 0), W.fixed_budget(80), None),
     (12, 1, 32, (6000, 31, 1900), W.fraction_budget(1, 16), None),
     (2, 8, 16, tuple(range(40, 40 * 34, 40)), W.fixed_budget(4), None),
+    # 136 units behind a table of 512 pages: the widest that one workgroup per unit takes
+    (2, 8, 16, (8175, 8176, 7169, 7168, 4096, 2049, 1, 0, 129) + (500,) * 8, W.fixed_budget(64), None),
 ]
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("append", [True, False])
 @pytest.mark.parametrize("case", range(len(CASES)))
-def test_step_equals_separate_calls(case, append):
+def test_step_equals_separate_calls(case, append, wide):
     G, Hkv, ps, lengths, sched, k_max = CASES[case]
-    log(f"case decode step {case} append={append}: G={G} Hkv={Hkv} ps={ps} lens={lengths}")
+    log(f"case decode step {case} append={append} wide={wide}: G={G} Hkv={Hkv} ps={ps} "
+        f"lens={lengths}")
     inp, meta, meta0, kn, vn = append_case(G, Hkv, ps, lengths, seed=500 + case,
-                                           schedule=sched, skip_last=False)
+                                           schedule=sched, skip_last=False, wide=wide)
+    narrow = one_workgroup_selection(len(lengths), Hkv, inp.max_pages)
+    assert narrow == (not wide and case != 4)   # (case 4: 12 units, 564 pages)
     if k_max is None:
         s = inp.workload.schedule
         k_max = S.budget_bound(inp.lens_host, ps, s.bin_tokens, s.min_pages, s.frac_num,
@@ -178,11 +185,12 @@ def test_step_matches_the_oracle():
     check_out(out.cpu().numpy().astype(np.float64), ref_out, "decode step")
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("sink,local", [(1, 0), (0, 3), (2, 2)])
-def test_step_forced_pages(sink, local):
-    log(f"case decode step, forced pages sink={sink} local={local}")
+def test_step_forced_pages(sink, local, wide):
+    log(f"case decode step, forced pages sink={sink} local={local} wide={wide}")
     inp, meta, _, kn, vn = append_case(2, 4, 16, (900, 40, 17, 3000), seed=530 + sink + local,
-                                       schedule=W.fixed_budget(6), skip_last=False)
+                                       schedule=W.fixed_budget(6), skip_last=False, wide=wide)
     assert unit_path(inp, 6)
     same_step(inp, meta, kn, vn, 6, sink=sink, local=local)
 
@@ -202,19 +210,22 @@ def test_step_schedule_too_long_to_stage():
     same_step(inp, meta, kn, vn, k_max)
 
 
-def test_step_bf16_output():
-    log("case decode step, bf16 output")
+@pytest.mark.parametrize("wide", [False, True])
+def test_step_bf16_output(wide):
+    log(f"case decode step, bf16 output wide={wide}")
     inp, meta, _, kn, vn = append_case(4, 2, 32, (700, 33, 8000), seed=550,
-                                       schedule=W.fixed_budget(10), skip_last=False)
+                                       schedule=W.fixed_budget(10), skip_last=False, wide=wide)
     same_step(inp, meta, kn, vn, 10, out_dtype=S.SPARROW_OUT_BF16)
 
 
-def test_step_mean_landmark():
-    log("case decode step, mean-key landmark")
+@pytest.mark.parametrize("wide", [False, True])
+def test_step_mean_landmark(wide):
+    log(f"case decode step, mean-key landmark wide={wide}")
     lengths = (2000, 300, 16, 4097)
     w = W.small(B=4, Hq=8, Hkv=4, ps=16, lengths=lengths, seed=560,
                 schedule=W.fixed_budget(12))
     inp = W.generate(w, DEV, lengths=list(lengths))
+    inp = widen(inp) if wide else inp
     lens = np.asarray(lengths, np.int32)
     meta = S.new_meta(inp.num_phys_pages, 4, DEV, landmark=S.SPARROW_LANDMARK_MEAN)
     S.page_meta_update(inp.k_cache, inp.block_table, torch.as_tensor(lens - 1, device=DEV), meta,
@@ -272,28 +283,30 @@ def test_step_full_size(cfg):
     same_step(inp, meta, kn, vn, k_max)
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("case", [0, 3, 6])
-def test_step_sequence_past_the_block_table(case):
+def test_step_sequence_past_the_block_table(case, wide):
     """The longest sequence gets a length one past what its block table addresses: the
     append leaves it alone and its length is clamped, in both forms of the step."""
     G, Hkv, ps, lengths, sched, _ = CASES[case]
-    log(f"case decode step {case}, a sequence past its block table")
+    log(f"case decode step {case}, a sequence past its block table wide={wide}")
     inp, meta, _, kn, vn = append_case(G, Hkv, ps, lengths, seed=590 + case, schedule=sched,
-                                       skip_last=True)
+                                       skip_last=True, wide=wide)
     s = inp.workload.schedule
     k_max = S.budget_bound(np.minimum(inp.lens_host, ps * inp.max_pages), ps, s.bin_tokens,
                            s.min_pages, s.frac_num, s.frac_den)
     same_step(inp, meta, kn, vn, k_max)
 
 
-@pytest.mark.parametrize("case", [0, 6])
-def test_step_absent_pages(case):
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("case", [0, 6, 9])
+def test_step_absent_pages(case, wide):
     """Block-table entries outside the cache inside the sequences (absent pages: scored 0,
     left out of the attention, no append to them) give the same results in both forms."""
     G, Hkv, ps, lengths, sched, _ = CASES[case]
-    log(f"case decode step {case}, absent pages")
+    log(f"case decode step {case}, absent pages wide={wide}")
     inp, meta, _, kn, vn = append_case(G, Hkv, ps, lengths, seed=600 + case, schedule=sched,
-                                       skip_last=False)
+                                       skip_last=False, wide=wide)
     bt = inp.block_table.clone()
     P = inp.num_phys_pages
     for b, L in enumerate(lengths):
@@ -332,18 +345,19 @@ def random_step_case(seed):
     return G, Hkv, ps, tuple(lengths), sched
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("seed", range(12))
-def test_random_shapes_whole_step(seed):
+def test_random_shapes_whole_step(seed, wide):
     """Seeded random shapes: the whole-step call equals the separate calls bit for bit, and
     its budgets, page lists and outputs match the CPU oracle's step after the append."""
     G, Hkv, ps, lengths, sched = random_step_case(seed)
     inp, meta, meta0, kn, vn = append_case(G, Hkv, ps, lengths, seed=610 + seed,
-                                           schedule=sched, skip_last=False)
+                                           schedule=sched, skip_last=False, wide=wide)
     s = inp.workload.schedule
     k_max = S.budget_bound(inp.lens_host, ps, s.bin_tokens, s.min_pages, s.frac_num,
                            s.frac_den)
     log(f"case decode step random {seed}: G={G} Hkv={Hkv} ps={ps} lens={lengths} "
-        f"k_max {k_max}, unit path {unit_path(inp, k_max)}")
+        f"k_max {k_max}, unit path {unit_path(inp, k_max)}, wide {wide}")
     h = host(inp)
     (k, idx, out), _ = same_step(inp, meta, kn, vn, k_max)
     kc, vc, _ = oracle.append_kv(W.bf16_bits(kn), W.bf16_bits(vn), h["k"], h["v"], h["bt"],

@@ -16,7 +16,7 @@ from paper_2606_08446_amd import sparrow as S
 from paper_2606_08446_amd import workloads as W
 
 from parity import (SCALE, check_indices, check_meta, check_out, full_check, gpu_run, host, log,
-                    oracle_budgets, sample_inputs)
+                    one_workgroup_selection, oracle_budgets, sample_inputs, widen)
 
 pytestmark = pytest.mark.gpu
 
@@ -58,8 +58,8 @@ SWEEP = [
     (4, 2, 64, (64, 65, 9000), W.fraction_budget(1, 5)),
     (2, 2, 128, (127, 128, 129, 30000), W.fraction_budget(1, 6)),
     (3, 2, 16, (0, 50, 0, 1200), W.fraction_budget(1, 2)),
-    # KV-head counts that leave a partial group of 8 heads per scoring workgroup, an odd
-    # head in a wave's head pair, or an idle wave
+    # KV-head counts that leave a partial group of 8 heads per workgroup of the split scoring, an
+    # odd head in a wave's head pair, or an idle wave
     (1, 9, 16, (3000, 17, 900), W.fraction_budget(1, 5)),
     (2, 12, 32, (5000, 64, 1), W.fraction_budget(1, 4)),
     (3, 5, 16, (2048, 2049, 333), W.fraction_budget(1, 3)),
@@ -68,20 +68,24 @@ SWEEP = [
     (6, 3, 64, (4000, 129, 7000), W.fraction_budget(1, 4)),
     (7, 2, 128, (2600, 257), W.fraction_budget(1, 2)),
     (12, 1, 32, (6000, 31, 1900), W.rising_permille(2048, 2048, 8192, 40, 200)),
-    # more KV heads than one scoring workgroup takes (8): two and four head blocks, the
-    # last partial
+    # more KV heads than a workgroup of the split scoring takes (8): two and four head
+    # blocks, the last partial
     (1, 16, 16, (3000, 70, 1), W.fraction_budget(1, 6)),
     (2, 20, 32, (2500, 900), W.fraction_budget(1, 5)),
     (1, 32, 64, (5000, 129), W.fixed_budget(9)),
 ]
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("case", range(len(SWEEP)))
-def test_small_sweep(case):
+def test_small_sweep(case, wide):
+    """Every case behind its own block table (one workgroup per unit up to 448 pages) and behind
+    a wide one (the split scoring and top-k)."""
     G, Hkv, ps, lengths, sched = SWEEP[case]
-    log(f"case sweep {case}: G={G} Hkv={Hkv} ps={ps} lens={lengths}")
+    log(f"case sweep {case}: G={G} Hkv={Hkv} ps={ps} lens={lengths} wide={wide}")
     inp = small_inputs(G, Hkv, ps, lengths, seed=100 + case, schedule=sched)
-    full_check(inp)
+    assert one_workgroup_selection(len(lengths), Hkv, inp.max_pages) == (inp.max_pages <= 448)
+    full_check(widen(inp) if wide else inp)
 
 
 
@@ -101,16 +105,18 @@ def replicated(inp, reps):
 
 @pytest.mark.parametrize("case", [0, 8, 10, 11, 12, 15])
 def test_scoring_workgroup_sizes_select_alike(case):
-    """A small batch is scored in 8-page workgroups; the same sequences repeated until the
-    grid holds 256 or more 32-page workgroups are scored in 32-page ones.  Both selections
-    equal the oracle's, and every copy of a sequence selects exactly the small batch's
-    pages (the scores are bit-identical)."""
+    """The split scoring, behind a wide block table: a small batch is scored in 8-page
+    workgroups; the same sequences repeated until the grid holds 256 or more 32-page
+    workgroups are scored in 32-page ones.  Both selections equal the oracle's, and every copy
+    of a sequence selects exactly the small batch's pages (the scores are bit-identical)."""
     G, Hkv, ps, lengths, sched = SWEEP[case]
-    inp = small_inputs(G, Hkv, ps, lengths, seed=100 + case, schedule=sched)
+    inp = widen(small_inputs(G, Hkv, ps, lengths, seed=100 + case, schedule=sched))
     blocks = -(-inp.max_pages // 32) * len(lengths) * -(-Hkv // 8)
     reps = -(-256 // blocks)
     assert blocks < 256 <= blocks * reps
     log(f"case block sizes {case}: G={G} Hkv={Hkv} ps={ps} lens={lengths} x{reps}")
+    for n in (1, reps):
+        assert not one_workgroup_selection(n * len(lengths), Hkv, inp.max_pages)
     small = full_check(inp)
     big = full_check(replicated(inp, reps))
     B = len(lengths)
@@ -143,11 +149,13 @@ def random_case(seed):
     return G, Hkv, ps, tuple(lengths), sched
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("seed", range(16))
-def test_random_shapes(seed):
+def test_random_shapes(seed, wide):
     G, Hkv, ps, lengths, sched = random_case(seed)
-    log(f"case random {seed}: G={G} Hkv={Hkv} ps={ps} lens={lengths}")
+    log(f"case random {seed}: G={G} Hkv={Hkv} ps={ps} lens={lengths} wide={wide}")
     inp = small_inputs(G, Hkv, ps, lengths, seed=700 + seed, schedule=sched)
+    inp = widen(inp) if wide else inp
     s = inp.workload.schedule
     k_max = S.budget_bound(inp.lens_host, ps, s.bin_tokens, s.min_pages, s.frac_num, s.frac_den)
     if seed % 4 == 3:
@@ -184,13 +192,14 @@ def many_bins(n_bins, seed):
                       tuple(int(x) for x in rng.integers(1, 10, n_bins)), 20)
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("n_bins", [256, 300])
-def test_schedule_tables_of_many_bins(n_bins):
-    # 256 bins: the scoring kernel stages the tables in LDS; more: it reads them from memory
-    log(f"case schedule of {n_bins} bins")
+def test_schedule_tables_of_many_bins(n_bins, wide):
+    # 256 bins: the split scoring stages the tables in LDS; more: it reads them from memory
+    log(f"case schedule of {n_bins} bins wide={wide}")
     lengths = (4000, 17, 4096, 4097, 6000, 1)  # several bins, the last bin and past it
     inp = small_inputs(3, 2, 16, lengths, seed=41, schedule=many_bins(n_bins, 5))
-    full_check(inp)
+    full_check(widen(inp) if wide else inp)
 
 
 def test_k_max_caps_the_budget():
@@ -245,14 +254,15 @@ def test_duplicated_pages_at_the_cut():
     assert r["gpu"]["idx"][0, 0, :2].tolist() == [10, 50]
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("perturb", [False, True])
-def test_many_pages_in_the_threshold_digit(perturb):
+def test_many_pages_in_the_threshold_digit(perturb, wide):
     """100 copies of one boosted page, budget 50: the radix select's threshold digit holds
     many keys pass after pass - down to the last bit for identical copies (ties to the lower
     index), or until the copies' scores, nudged apart in one channel each, separate.  With 8
-    units (512-thread top-k) and with the batch repeated to 1024 units (256-thread top-k),
-    which must select alike."""
-    log(f"case many pages in the threshold digit, perturbed {perturb}")
+    units (512 threads) and with the batch repeated to 1024 units (256 threads), which must
+    select alike; in the kernel that scores and selects, and in the top-k kernel."""
+    log(f"case many pages in the threshold digit, perturbed {perturb} wide={wide}")
     inp = small_inputs(2, 8, 16, (3000,), seed=14, schedule=W.fixed_budget(50))
     bt = inp.block_table.cpu().numpy()
     src = int(bt[0, 150])
@@ -264,6 +274,7 @@ def test_many_pages_in_the_threshold_digit(perturb):
             c = j % 128
             v = inp.k_cache[dst, :, :, c].float()
             inp.k_cache[dst, :, :, c] = (v * (1.0 + (j + 1) / 512.0)).to(torch.bfloat16)
+    inp = widen(inp) if wide else inp
     small = full_check(inp)
     if not perturb:
         for h in range(8):   # the 50 lowest of the 101 identical pages

@@ -2,19 +2,24 @@
 
 Which of the two a call takes depends on its units and on the block table's width, so the
 same sequences run both ways: all together behind a narrow table, and a few at a time behind a
-wide one (the split kernels, which the oracle tests cover).  Page counts sit at the edges of
-a wave's batch (16 pages), of a round over the waves (64 or 128) and of a block-table group
-(256 or 512), with both workgroup sizes; with and without the append, both landmarks, forced
-pages, more than eight query heads per KV head, absent pages, lengths of 0 and past the table."""
+wide one (the split kernels, which the oracle tests cover behind wide tables).  Page counts
+sit at the edges of a wave's batch (16 pages), of a round over the waves (64 or 128), of a
+block-table group (256 pages with four waves; eight waves' first group is the widest table) and of the
+narrow tables themselves, with both workgroup sizes; with and without the append, both
+landmarks, forced pages, more than eight query heads per KV head, absent pages in both groups,
+lengths of 0 and past the table."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2606_08446_amd import sparrow as S
 
+from parity import one_workgroup_selection
+
 pytestmark = pytest.mark.gpu
 
-EDGES = [0, 1, 2, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300, 511, 512]
+EDGES = [0, 1, 2, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300, 511, 512, 271, 272,
+         273, 319, 320, 321, 447, 448, 449]
 
 
 def select(x, rows, width, append, landmark, sink, local, k_max):
@@ -38,9 +43,9 @@ def select(x, rows, width, append, landmark, sink, local, k_max):
 
 
 @pytest.mark.parametrize("B,hkv,group,width", [
-    (18, 2, 3, 512), (18, 3, 12, 512),    # few units, 512 threads
-    (72, 2, 1, 600), (72, 2, 2, 2048),    # 128 units and more, tables past 512 pages
-    (520, 1, 4, 512), (520, 1, 2, 800),   # 512 units and more: 256 threads, then 512
+    (27, 2, 3, 448), (27, 3, 12, 448),    # few units, 512 threads
+    (72, 2, 1, 512), (72, 2, 2, 480),     # 128 units and more
+    (520, 1, 4, 512), (520, 1, 2, 449),   # 512 units and more: 256 threads
 ])
 @pytest.mark.parametrize("append,landmark,sink,local", [
     (True, S.SPARROW_LANDMARK_MINMAX, 0, 0), (False, S.SPARROW_LANDMARK_MINMAX, 1, 3),
@@ -49,7 +54,8 @@ def select(x, rows, width, append, landmark, sink, local, k_max):
 def test_paths_agree(gpu_device, B, hkv, group, width, append, landmark, sink, local):
     ps = 16
     rng = np.random.default_rng(width + hkv)
-    pages = np.resize(EDGES, B)
+    assert one_workgroup_selection(B, hkv, width)
+    pages = np.minimum(np.resize(EDGES, B), width)
     lens = np.where(pages > 0, (pages - 1) * ps + rng.integers(1, ps + 1, B), 0).astype(np.int32)
     P = int(pages.max()) * 2          # sequences share physical pages unless they append
     bt = np.stack([rng.permutation(P)[:512] for _ in range(B)]).astype(np.int32)
@@ -59,7 +65,8 @@ def test_paths_agree(gpu_device, B, hkv, group, width, append, landmark, sink, l
             bt[b, n - 1] = P - B + b
     bt[3, 7] = P + 5                  # absent pages
     bt[9, 100] = -2
-    lens[5] = width * ps + 40 if width <= 512 else lens[5]   # past the table: no append
+    bt[16, 300] = P + 9               # past the first block-table group of four waves
+    lens[5] = width * ps + 40         # past the table: no append
     g = torch.Generator(device="cuda").manual_seed(width)
 
     def randn(*shape):
@@ -76,9 +83,10 @@ def test_paths_agree(gpu_device, B, hkv, group, width, append, landmark, sink, l
                        landmark=landmark)
     k_max = 200
     got = select(x, list(range(B)), width, append, landmark, sink, local, k_max)
-    few = 36                          # below 128 units: split behind a wide table
+    few = 36
+    assert not one_workgroup_selection(few, hkv, 2100)
     for r0 in range(0, min(B, 180), few):
-        rows = [r for r in range(r0, min(B, r0 + few)) if lens[r] <= 512 * ps]
+        rows = [r for r in range(r0, min(B, r0 + few)) if r != 5]
         want = select(x, rows, 2100, append, landmark, sink, local, k_max)
         assert torch.equal(got[0][rows], want[0])
         assert torch.equal(got[1][rows], want[1])

@@ -12,7 +12,7 @@ import oracle
 from paper_2606_08446_amd import sparrow as S
 from paper_2606_08446_amd import workloads as W
 
-from parity import NEAR_TIE, SCALE, check_out, host, log, oracle_budgets, sample_inputs
+from parity import NEAR_TIE, SCALE, check_out, host, log, oracle_budgets, sample_inputs, widen
 
 pytestmark = pytest.mark.gpu
 
@@ -77,10 +77,17 @@ def test_mean_metadata_matches_oracle_bitwise(ps):
     np.testing.assert_array_equal(meta2.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("copies", [0, 1, 5])   # 0: one workgroup per unit
 @pytest.mark.parametrize("G,Hkv,ps", [(2, 2, 16), (5, 3, 32), (1, 9, 16), (4, 8, 64)])
-def test_mean_selection_and_attention_match_oracle(G, Hkv, ps):
-    log(f"case mean select G={G} Hkv={Hkv} ps={ps}")
-    inp = small(G, Hkv, ps, (ps * 40 + 5, ps * 3, 700, 17), seed=60 + G, hot_pages=3)
+def test_mean_selection_and_attention_match_oracle(G, Hkv, ps, copies):
+    """Behind a wide block table in 8-page workgroups (4 sequences) and 32-page ones (20)."""
+    log(f"case mean select G={G} Hkv={Hkv} ps={ps} copies={copies}")
+    inp = small(G, Hkv, ps, (ps * 40 + 5, ps * 3, 700, 17) * max(1, copies), seed=60 + G,
+                hot_pages=3)
+    if copies:
+        inp = widen(inp)
+        blocks = -(-inp.max_pages // 32) * 4 * copies * -(-Hkv // 8)
+        assert (blocks < 256) == (copies == 1)
     h = host(inp)
     s = inp.workload.schedule
     k_max = inp.max_pages
@@ -104,12 +111,14 @@ def test_mean_selection_and_attention_match_oracle(G, Hkv, ps):
     check_out(out.cpu().numpy().astype(np.float64), ref, "mean-landmark sparse")
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("landmark", [S.SPARROW_LANDMARK_MINMAX, MEAN])
 @pytest.mark.parametrize("sink,local", [(1, 0), (0, 3), (2, 2), (40, 40)])
-def test_forced_pages_match_oracle(landmark, sink, local):
-    log(f"case forced sink={sink} local={local} landmark={landmark}")
+def test_forced_pages_match_oracle(landmark, sink, local, wide):
+    log(f"case forced sink={sink} local={local} landmark={landmark} wide={wide}")
     inp = small(4, 2, 16, (16 * 60, 16 * 5 + 9, 300, 16 * 200 + 1), seed=70,
                 schedule=W.fraction_budget(1, 8, floor_pages=3))
+    inp = widen(inp) if wide else inp
     h = host(inp)
     s = inp.workload.schedule
     k_max = inp.max_pages
@@ -151,10 +160,12 @@ def run_fused(inp, meta, kn, vn, k_max, landmark):
     return k, idx
 
 
-def test_mean_append_alone_and_fused():
-    log("case mean append")
+@pytest.mark.parametrize("wide", [False, True])
+def test_mean_append_alone_and_fused(wide):
+    log(f"case mean append wide={wide}")
     lengths = (33, 64, 17, 100, 1)
     inp = small(3, 2, 16, lengths, seed=80)
+    inp = widen(inp) if wide else inp
     h = host(inp)
     before = np.maximum(h["lens"] - 1, 0).astype(np.int32)
     sums0 = oracle.page_key_sums(h["k"], h["bt"], before)
