@@ -44,12 +44,12 @@ ENTRY = {
                     ("attention.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
     "dense_attn": ("k_attn_stream<dense> + k_attn_merge",
                    ("attention.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
-    "append_score_topk": ("k_score_select (with append), or k_page_score + k_topk",
+    "append_score_topk": ("k_page_score + k_topk, or k_score_select (with append)",
                           ("score_topk.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
-    "score_topk": ("k_score_select, or k_page_score + k_topk",
+    "score_topk": ("k_page_score + k_topk, or k_score_select",
                    ("score_topk.hip", "score_unit.h", "topk.h", "common.h", "wave.h")),
     "decode_step": ("k_decode_unit, or k_page_score (with append) + k_select_attn_unit, or "
-                    "k_score_select + k_attn_stream<sparse> + k_attn_merge",
+                    "the kernels of append_score_topk + k_attn_stream<sparse> + k_attn_merge",
                     ("score_topk.hip", "score_unit.h", "attention.hip", "topk.h", "common.h",
                      "wave.h")),
     "append": ("k_append_kv", ("append.hip", "common.h")),

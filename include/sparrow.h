@@ -36,6 +36,10 @@
  *    indices, lengths and budgets are clamped to what the shape allows (a
  *    negative length is an empty sequence; one beyond max_pages_per_seq *
  *    page_size tokens counts as that many, and its token is not appended).
+ *  - Inputs must not change while a call's kernels run (order other streams'
+ *    writes before them): seq_lens and the block table are read more than once,
+ *    and workgroups that saw different lengths would split the work differently
+ *    and use workspace that none of them wrote.
  *  - bf16 tensors are IEEE bfloat16 bit patterns.  NaN inputs are not supported.
  *  - Alignment: q, k_cache, v_cache, meta, out and workspace start on a 16-byte
  *    boundary and the int32 arrays on a 4-byte boundary (any hipMalloc or PyTorch

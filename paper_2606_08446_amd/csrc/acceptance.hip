@@ -12,8 +12,10 @@
 // rest and more than a few tokens, the kept vectors are read non-temporally to leave the caches
 // to it.
 //
-// What bounds it: fp32 rows their traffic (1.5 times the rows, at 7.5 TB/s), bf16 rows the
-// arithmetic and the turns between the passes.  With one token per workgroup the memory was
+// What bounds it: fp32 rows their traffic (the loads ask for 1.56 times the rows of Qwen3's
+// vocabulary, at 7.5 TB/s, some of the second reading being served by the caches), bf16 rows
+// the arithmetic and the turns between the passes.  The fp32 kernel spills 3 registers at 21
+// kept vectors; with 20 it spills none and was 1-2 % slower on those rows.  With one token per workgroup the memory was
 // idle while the second pass computed and the VALU idle while a new token's rows arrived;
 // now the second pass replaces every kept vector by the next token's as soon as it is used,
 // the other vectors roll through three slots per row, and one barrier a token joins the
